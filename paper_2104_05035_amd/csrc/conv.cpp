@@ -2,7 +2,8 @@
 // workspace.  bf16 stride-1 convolutions with kernel 3 (pad 1) or 1 (pad 0)
 // and suitable channel counts take the LDS-brick kernels (1^3 weight
 // gradients a direct GEMM); the single-channel 7^3 stride-2 stem has its own
-// kernels; every other shape is served by the generic gather implicit GEMM.
+// kernels; float32 convolutions up to 7^3 take the voxel-box kernels; every
+// other shape is served by the generic gather implicit GEMM.
 #include "kernels.hpp"
 
 namespace rat3d {
@@ -11,6 +12,7 @@ static size_t wgrad_ws(const ConvGeom& g, rat3d_dtype dt) {
     if (stem_wgrad_ok(g, dt)) return stem_wgrad_ws(g);
     if (brick_wgrad_ok(g, dt)) return brick_wgrad_ws(g);
     if (pw_wgrad_ok(g, dt)) return pw_wgrad_ws(g);
+    if (box_wgrad_ok(g, dt)) return box_wgrad_ws(g);
     return wgrad_gather_ws(g);
 }
 
@@ -30,6 +32,7 @@ rat3d_status conv_fwd(const ConvGeom& g, rat3d_dtype dt, const void* x, const vo
     (void)ws_bytes;
     if (stem_ok(g, dt) && !bias) return conv_fwd_stem(g, x, w, y, ws, st);
     if (brick_fd_ok(g, dt, false)) return conv_fd_brick(g, false, x, w, bias, y, 0, ws, st);
+    if (box_fd_ok(g, dt, false)) return conv_fd_box(g, false, x, w, bias, y, 0, st);
     return conv_fwd_gather(g, dt, x, w, bias, y, st);
 }
 
@@ -38,6 +41,7 @@ rat3d_status conv_dgrad(const ConvGeom& g, rat3d_dtype dt, const void* dy, const
     (void)ws_bytes;
     if (brick_fd_ok(g, dt, true))
         return conv_fd_brick(g, true, dy, w, nullptr, dx, accumulate, ws, st);
+    if (box_fd_ok(g, dt, true)) return conv_fd_box(g, true, dy, w, nullptr, dx, accumulate, st);
     return conv_dgrad_gather(g, dt, dy, w, dx, accumulate, st);
 }
 
@@ -81,6 +85,7 @@ rat3d_status conv_wgrad(const ConvGeom& g, rat3d_dtype dt, const void* x, const 
     if (stem_wgrad_ok(g, dt)) s = conv_wgrad_stem(g, x, dy, dw, accumulate, ws, st);
     else if (brick_wgrad_ok(g, dt)) s = conv_wgrad_brick(g, x, dy, dw, accumulate, ws, st);
     else if (pw_wgrad_ok(g, dt)) s = conv_wgrad_pw(g, x, dy, dw, accumulate, ws, st);
+    else if (box_wgrad_ok(g, dt)) s = conv_wgrad_box(g, x, dy, dw, accumulate, ws, st);
     else s = conv_wgrad_gather(g, dt, x, dy, dw, accumulate, ws, st);
     if (s != RAT3D_OK) return s;
     if (db) {

@@ -74,6 +74,15 @@ rat3d_status conv_bias_grad(const ConvGeom& g, rat3d_dtype dt, const void* dy, f
 rat3d_status wgrad_reduce_launch(const float* part, int splits, int64_t count, float* dw,
                                  int accumulate, hipStream_t st);
 
+// ---- float32 convolutions over voxel boxes, k <= 7 (conv_box.hip) --------
+bool box_fd_ok(const ConvGeom& g, rat3d_dtype dt, bool dgrad);
+rat3d_status conv_fd_box(const ConvGeom& g, bool dgrad, const void* src, const void* w,
+                         const float* bias, void* dst, int accumulate, hipStream_t st);
+bool box_wgrad_ok(const ConvGeom& g, rat3d_dtype dt);
+size_t box_wgrad_ws(const ConvGeom& g);  // at most wgrad_gather_ws or 24 MiB
+rat3d_status conv_wgrad_box(const ConvGeom& g, const void* x, const void* dy, float* dw,
+                            int accumulate, void* ws, hipStream_t st);
+
 // ---- LDS-brick kernels for bf16, stride 1, k in {1, 3} (conv_brick.hip) ---
 bool brick_fd_ok(const ConvGeom& g, rat3d_dtype dt, bool dgrad);
 bool brick_wgrad_ok(const ConvGeom& g, rat3d_dtype dt);
