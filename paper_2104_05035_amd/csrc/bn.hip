@@ -143,7 +143,14 @@ __global__ __launch_bounds__(kBnThreads) void bn_fwd_stats(const T* __restrict__
 // RES: 0 no residual, 1 y += r, 2 y += BN_r(r) with the residual's own batch
 // norm (no ReLU) formed here from its statistics partials `rst` and rounded as
 // its own apply would store it.
-template <typename T, int VEC, bool RELU, int RES>
+//
+// ODD: planes of any V (RES 0 or 1, no bits).  The tensors start at 16-byte
+// boundaries, a plane may not: the vectors are the 16-byte units of the
+// tensor, so the first and last one of a plane may belong to it in part and
+// are loaded and stored by element.  Element by element throughout (256 or
+// 1024 elements per block, each block forming its coefficients) took 197 us
+// forward and 169 us backward at 4 x 64 x 46x55x46 in bf16, these 40 and 50.
+template <typename T, int VEC, bool RELU, int RES, bool ODD = false>
 __global__ __launch_bounds__(kBnThreads) void bn_fwd_apply(const T* __restrict__ x,
                                                            const T* __restrict__ r, int N, int C,
                                                            int64_t V, unsigned cpp,
@@ -154,9 +161,10 @@ __global__ __launch_bounds__(kBnThreads) void bn_fwd_apply(const T* __restrict__
     constexpr int64_t kStep = (int64_t)kBnThreads * VEC;
     const int plane = (int)(blockIdx.x / cpp);  // wave-uniform
     const unsigned chunk = blockIdx.x - (unsigned)plane * cpp;
-    const int64_t e0 = (int64_t)chunk * kStep * U + (int64_t)threadIdx.x * VEC;
     const int c = plane % C;
     const int64_t base = (int64_t)plane * V;
+    const int64_t e0 = (int64_t)chunk * kStep * U + (int64_t)threadIdx.x * VEC -
+                       (ODD ? base & (VEC - 1) : 0);
     // every vector is loaded before the coefficients are formed; vectors past
     // the end load the plane's last vector (V % VEC == 0), so every lane takes
     // part in the coefficient reduction, and store nothing
@@ -165,9 +173,19 @@ __global__ __launch_bounds__(kBnThreads) void bn_fwd_apply(const T* __restrict__
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         const int64_t e = e0 + u * kStep;
-        const int64_t i = base + (e < V ? e : V - VEC);
-        vload<T, VEC>(x + i, v[u]);
-        if constexpr (RES) vload<T, VEC>(r + i, rv[u]);
+        if constexpr (ODD) {
+            if (e >= 0 && e + VEC <= V) {
+                vload<T, VEC>(x + base + e, v[u]);
+                if constexpr (RES) vload<T, VEC>(r + base + e, rv[u]);
+            } else {
+                vload_part<T, VEC>(x + base, e, V, v[u]);
+                if constexpr (RES) vload_part<T, VEC>(r + base, e, V, rv[u]);
+            }
+        } else {
+            const int64_t i = base + (e < V ? e : V - VEC);
+            vload<T, VEC>(x + i, v[u]);
+            if constexpr (RES) vload<T, VEC>(r + i, rv[u]);
+        }
     }
     float sc, sh;
     const bool owner = plane < C && chunk == 0 && threadIdx.x == 0;
@@ -190,7 +208,7 @@ __global__ __launch_bounds__(kBnThreads) void bn_fwd_apply(const T* __restrict__
             if constexpr (RELU) o = fmaxf(o, 0.f);
             v[u][j] = o;
         }
-        if constexpr (sizeof(T) == 2 && VEC == 8) {
+        if constexpr (sizeof(T) == 2 && VEC == 8 && !ODD) {
             if (ybits) {
                 // the stored bf16 values, and bit j = (y_j > 0) of them
                 uint32_t w[4];
@@ -204,6 +222,12 @@ __global__ __launch_bounds__(kBnThreads) void bn_fwd_apply(const T* __restrict__
                     byte |= ((int16_t)(w[q] >> 16) > 0 ? 1u : 0u) << (2 * q + 1);
                 }
                 ybits[(base + e) >> 3] = (uint8_t)byte;
+                continue;
+            }
+        }
+        if constexpr (ODD) {
+            if (e < 0 || e + VEC > V) {
+                vstore_part<T, VEC>(y + base, e, V, v[u]);
                 continue;
             }
         }
@@ -282,7 +306,8 @@ __global__ __launch_bounds__(kBnThreads) void bn_bwd_stats(const T* __restrict__
 }
 
 // DRES: 0 no residual gradient, 1 dres = g, 2 dres += g (one rounding).
-template <typename T, int VEC, int MASK, int DRES>
+// ODD: as in bn_fwd_apply.
+template <typename T, int VEC, int MASK, int DRES, bool ODD = false>
 __global__ __launch_bounds__(kBnThreads) void bn_bwd_apply(
     const T* __restrict__ dy, const T* __restrict__ x, const T* __restrict__ y,
     const uint8_t* __restrict__ ybits, int N, int C, int64_t V, unsigned cpp,
@@ -292,9 +317,10 @@ __global__ __launch_bounds__(kBnThreads) void bn_bwd_apply(
     constexpr int64_t kStep = (int64_t)kBnThreads * VEC;
     const int plane = (int)(blockIdx.x / cpp);  // wave-uniform
     const unsigned chunk = blockIdx.x - (unsigned)plane * cpp;
-    const int64_t e0 = (int64_t)chunk * kStep * U + (int64_t)threadIdx.x * VEC;
     const int c = plane % C;
     const int64_t base = (int64_t)plane * V;
+    const int64_t e0 = (int64_t)chunk * kStep * U + (int64_t)threadIdx.x * VEC -
+                       (ODD ? base & (VEC - 1) : 0);
     // as in the forward apply: every load first (clamped), every lane in the
     // coefficient reduction
     float g[U][VEC], xv[U][VEC];
@@ -303,12 +329,19 @@ __global__ __launch_bounds__(kBnThreads) void bn_bwd_apply(
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         const int64_t e = e0 + u * kStep;
-        const int64_t i = base + (e < V ? e : V - VEC);
-        vload<T, VEC>(dy + i, g[u]);
-        vload<T, VEC>(x + i, xv[u]);
-        if constexpr (MASK == kMaskY) vload<T, VEC>(y + i, yv[u]);
-        if constexpr (MASK == kMaskBits) yb[u] = ybits[i >> 3];
-        if constexpr (DRES == 2) vload<T, VEC>(dres + i, ov[u]);
+        if (ODD && !(e >= 0 && e + VEC <= V)) {
+            vload_part<T, VEC>(dy + base, e, V, g[u]);
+            vload_part<T, VEC>(x + base, e, V, xv[u]);
+            if constexpr (MASK == kMaskY) vload_part<T, VEC>(y + base, e, V, yv[u]);
+            if constexpr (DRES == 2) vload_part<T, VEC>(dres + base, e, V, ov[u]);
+        } else {
+            const int64_t i = base + (ODD || e < V ? e : V - VEC);
+            vload<T, VEC>(dy + i, g[u]);
+            vload<T, VEC>(x + i, xv[u]);
+            if constexpr (MASK == kMaskY) vload<T, VEC>(y + i, yv[u]);
+            if constexpr (MASK == kMaskBits) yb[u] = ybits[i >> 3];
+            if constexpr (DRES == 2) vload<T, VEC>(dres + i, ov[u]);
+        }
     }
     float k, a, b;
     bn_bwd_coefs(N, V, c, st, plane < C && chunk == 0 && threadIdx.x == 0, k, a, b);
@@ -330,19 +363,41 @@ __global__ __launch_bounds__(kBnThreads) void bn_bwd_apply(
 #pragma unroll
             for (int j = 0; j < VEC; ++j) g[u][j] = fmaf(xv[u][j], fsc, fsh) > 0.f ? g[u][j] : 0.f;
         }
-        if constexpr (DRES == 1) vstore<T, VEC>(dres + i, g[u]);
         if constexpr (DRES == 2) {
 #pragma unroll
             for (int j = 0; j < VEC; ++j) ov[u][j] += g[u][j];
-            vstore<T, VEC>(dres + i, ov[u]);
         }
 #pragma unroll
         for (int j = 0; j < VEC; ++j) xv[u][j] = k * (g[u][j] - a - (xv[u][j] - mean) * b);
-        vstore<T, VEC>(dx + i, xv[u]);
+        if (ODD && (e < 0 || e + VEC > V)) {
+            if constexpr (DRES == 1) vstore_part<T, VEC>(dres + base, e, V, g[u]);
+            if constexpr (DRES == 2) vstore_part<T, VEC>(dres + base, e, V, ov[u]);
+            vstore_part<T, VEC>(dx + base, e, V, xv[u]);
+        } else {
+            if constexpr (DRES == 1) vstore<T, VEC>(dres + i, g[u]);
+            if constexpr (DRES == 2) vstore<T, VEC>(dres + i, ov[u]);
+            vstore<T, VEC>(dx + i, xv[u]);
+        }
     }
 }
 
 // ---------------------------------------------------------------- launchers
+// Whether planes of V elements that are no whole vectors (VEC == 1) take the
+// ODD apply: below 1024 one block of 256 elements per plane or two are quicker
+// than vectors with their partial ends (the full network's 36- and
+// 252-element planes: its step 6.47 ms, 6.55 with vectors).
+template <int VEC> static bool bn_odd_vec(int64_t V) { return VEC == 1 && V >= 1024; }
+
+// Blocks per plane of an apply pass, u vectors per thread; an odd plane may
+// lie in one more vector than it fills.
+template <typename T, int VEC> static unsigned bn_chunks(int64_t V, int u) {
+    constexpr int AV = vec16<T>();
+    const int64_t vecs = bn_odd_vec<VEC>(V) ? (V + 2 * AV - 2) / AV : V / VEC;
+    return (unsigned)ceil_div(vecs, (int64_t)kBnThreads * u);
+}
+
+// VEC: 1 where V is not a multiple of the 16-byte vector (element-wise
+// statistics), else that vector's width.
 template <typename T, int VEC>
 static rat3d_status bn_fwd_t(const BnGeom& g, int relu, float eps, float momentum, const T* x,
                              const T* r, const float* gamma, const float* beta, T* y,
@@ -361,12 +416,19 @@ static rat3d_status bn_fwd_t(const BnGeom& g, int relu, float eps, float momentu
     const BnFwdStats fs{part,     sl.per_channel, gamma,   beta,   eps,      momentum,
                         save_mean, save_invstd,   run_mean, run_var, save_coef};
     const int fu = r ? fwd_apply_u<1>() : fwd_apply_u<0>();
-    const unsigned cpp = (unsigned)ceil_div(g.V / VEC, kBnThreads * fu);  // chunks per plane
+    const bool odd = bn_odd_vec<VEC>(g.V);
+    const unsigned cpp = bn_chunks<T, VEC>(g.V, fu);  // chunks per plane
     const unsigned grid = cpp * (unsigned)(g.N * g.C);
     ProfScope ps("bn_fwd_apply", st, 0.0, tb * (r ? 3 : 2) + (ybits ? tb / 16 : 0.0));
 #define RAT3D_BN_FWD(RL, RS)                                                                 \
-    bn_fwd_apply<T, VEC, RL, RS><<<grid, kBnThreads, 0, st>>>(x, r, g.N, g.C, g.V, cpp, fs, y, \
-                                                              ybits, BnFwdStats{})
+    do {                                                                                     \
+        if (odd)                                                                             \
+            bn_fwd_apply<T, vec16<T>(), RL, RS, true><<<grid, kBnThreads, 0, st>>>(          \
+                x, r, g.N, g.C, g.V, cpp, fs, y, ybits, BnFwdStats{});                       \
+        else                                                                                 \
+            bn_fwd_apply<T, VEC, RL, RS><<<grid, kBnThreads, 0, st>>>(                       \
+                x, r, g.N, g.C, g.V, cpp, fs, y, ybits, BnFwdStats{});                       \
+    } while (0)
     if (relu && r) RAT3D_BN_FWD(true, 1);
     else if (relu) RAT3D_BN_FWD(true, 0);
     else if (r) RAT3D_BN_FWD(false, 1);
@@ -402,13 +464,20 @@ static rat3d_status bn_bwd_t(const BnGeom& g, int relu, const T* dy, const T* x,
     RAT3D_LAUNCH_CHECK();
     }
     const BnBwdStats bs{part, sl.per_channel, gamma, save_invstd, dgamma, dbeta, accumulate};
-    const unsigned cpp = (unsigned)ceil_div(g.V / VEC, kBnThreads * kBwdApplyU);  // chunks per plane
+    const bool odd = bn_odd_vec<VEC>(g.V);
+    const unsigned cpp = bn_chunks<T, VEC>(g.V, kBwdApplyU);  // chunks per plane
     const unsigned grid = cpp * (unsigned)(g.N * g.C);
     ProfScope ps("bn_bwd_apply", st, 0.0,
                  tb * (3 + (dres ? (dres_acc ? 2 : 1) : 0)) + mb);
-#define RAT3D_BN_BWD(M, D)                                                                    \
-    bn_bwd_apply<T, VEC, M, D><<<grid, kBnThreads, 0, st>>>(dy, x, y, ybits, g.N, g.C, g.V, cpp, \
-                                                            save_mean, fwd_coef, bs, dx, dres)
+#define RAT3D_BN_BWD(M, D)                                                                \
+    do {                                                                                  \
+        if (odd)                                                                          \
+            bn_bwd_apply<T, vec16<T>(), M, D, true><<<grid, kBnThreads, 0, st>>>(         \
+                dy, x, y, ybits, g.N, g.C, g.V, cpp, save_mean, fwd_coef, bs, dx, dres);  \
+        else                                                                              \
+            bn_bwd_apply<T, VEC, M, D><<<grid, kBnThreads, 0, st>>>(                      \
+                dy, x, y, ybits, g.N, g.C, g.V, cpp, save_mean, fwd_coef, bs, dx, dres);  \
+    } while (0)
 #define RAT3D_BN_BWD_M(M)                      \
     if (dmode == 2) RAT3D_BN_BWD(M, 2);        \
     else if (dmode == 1) RAT3D_BN_BWD(M, 1);   \

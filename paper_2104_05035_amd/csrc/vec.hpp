@@ -45,6 +45,22 @@ __device__ __forceinline__ void vstore(T* __restrict__ p, const float (&o)[VEC])
     }
 }
 
+// The elements e .. e + VEC - 1 of p that lie in [0, V), one by one (others
+// load as zero and are not stored).
+template <typename T, int VEC>
+__device__ __forceinline__ void vload_part(const T* __restrict__ p, int64_t e, int64_t V,
+                                           float (&o)[VEC]) {
+#pragma unroll
+    for (int j = 0; j < VEC; ++j) o[j] = e + j >= 0 && e + j < V ? Elt<T>::ld(p + e + j) : 0.f;
+}
+template <typename T, int VEC>
+__device__ __forceinline__ void vstore_part(T* __restrict__ p, int64_t e, int64_t V,
+                                            const float (&o)[VEC]) {
+#pragma unroll
+    for (int j = 0; j < VEC; ++j)
+        if (e + j >= 0 && e + j < V) Elt<T>::st(p + e + j, o[j]);
+}
+
 // Natural 16-byte vector width of T.
 template <typename T> constexpr int vec16() { return 16 / (int)sizeof(T); }
 
