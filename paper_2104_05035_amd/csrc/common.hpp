@@ -109,6 +109,15 @@ __device__ __forceinline__ int xcd_remap(int bid, int nb) {
     return (bid & 7) * q + (bid >> 3);
 }
 
+// i / d for 0 <= i, d < 2^16 by one multiplication; the reciprocal is wave-uniform.
+struct Div {
+    uint32_t d, m;
+    __device__ __forceinline__ explicit Div(int x) : d((uint32_t)x), m(x > 1 ? 0xffffffffu / x + 1 : 0) {}
+    __device__ __forceinline__ int operator()(int i) const {
+        return d > 1 ? (int)__umulhi((uint32_t)i, m) : i;
+    }
+};
+
 __host__ __device__ __forceinline__ int64_t ceil_div(int64_t a, int64_t b) {
     return (a + b - 1) / b;
 }

@@ -57,15 +57,6 @@ __device__ __forceinline__ float buf_ldf(__amdgpu_buffer_rsrc_t r, uint32_t off)
     return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
 }
 
-// i / d for 0 <= i, d < 2^16 by one multiplication; the reciprocal is wave-uniform.
-struct Div {
-    uint32_t d, m;
-    __device__ __forceinline__ explicit Div(int x) : d((uint32_t)x), m(x > 1 ? 0xffffffffu / x + 1 : 0) {}
-    __device__ __forceinline__ int operator()(int i) const {
-        return d > 1 ? (int)__umulhi((uint32_t)i, m) : i;
-    }
-};
-
 struct FdBox {
     const float* src;   // [N][Cs][Sd][Sh][Sw]
     const float* w;     // [Co][Ci][k^3]

@@ -1,0 +1,52 @@
+"""GPU parity of the passes for maps of any size at the places where their
+blocks and vectors end: planes that start and end inside a 16-byte unit, one
+or several chunks of a plane, volumes of several blocks with a short last
+one, resampling by less than 1, to the same size and by almost 3, planes too
+large for the staged kernels."""
+import pytest
+
+from tests.test_gpu_ops import test_bn as check_bn
+from tests.test_gpu_ops import test_maxpool as check_maxpool
+from tests.test_gpu_ops import test_trilinear as check_trilinear
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("case", [
+    (2, 3, 7, 9, 11, "bf16"), (3, 5, 1, 1, 1, "bf16"), (2, 3, 1, 1, 9, "bf16"),
+    (2, 2, 13, 15, 23, "bf16"), (1, 3, 19, 21, 25, "bf16"), (2, 3, 7, 9, 11, "f32"),
+    (2, 2, 13, 15, 23, "f32"), (3, 3, 1, 1, 5, "f32"), (5, 1, 1, 2, 1, "f32"),
+], ids=lambda c: "%dx%dx%dx%dx%d_%s" % c)
+@pytest.mark.parametrize("relu,resid", [(1, False), (0, False), (1, True), (0, True)])
+def test_bn_odd(case, relu, resid):
+    check_bn(case, relu, resid)
+
+
+@pytest.mark.parametrize("case", [
+    (1, 3, 9, 11, 13, "bf16"), (2, 2, 46, 55, 46, "bf16"), (1, 1, 7, 70, 70, "bf16"),
+    (2, 3, 12, 14, 12, "f32"), (1, 2, 5, 41, 39, "f32"), (1, 1, 3, 80, 90, "f32"),
+    (3, 1, 1, 1, 2, "f32"), (1, 1, 4, 16, 24, "f32"),
+], ids=lambda c: "%dx%dx%dx%dx%d_%s" % c)
+def test_maxpool_any(case):
+    check_maxpool(case)
+
+
+# The kernels form an axis position as (o + 1/2) * (in / out) - 1/2 in float32:
+# with an inexact ratio its error is up to |position| 2^-23, which moves the
+# weights by as much and an output by that times the difference of neighbouring
+# inputs -- more than 2^-16 of the sum of |terms| where the heavier terms happen
+# to be small.  The float32 cases therefore have ratios that float32 holds
+# exactly; the others are small maps in bf16, whose outputs are coarser than
+# this error except next to zero.
+EXACT = [((23, 28, 23), (46, 56, 46)), ((6, 5, 9), (8, 8, 12)), ((4, 6, 10), (2, 3, 5)),
+         ((3, 3, 3), (3, 3, 3)), ((5, 5, 15), (8, 8, 16)), ((1, 1, 1), (3, 2, 3)),
+         ((2, 60, 50), (4, 120, 100))]
+ANY = [((23, 28, 23), (46, 55, 46)), ((7, 5, 9), (13, 10, 17)), ((4, 6, 5), (2, 3, 4)),
+       ((2, 3, 5), (6, 8, 14)), ((9, 4, 2), (10, 5, 2))]
+
+
+@pytest.mark.parametrize("sizes,dt", [(s, d) for s in EXACT for d in ("f32", "bf16")] +
+                         [(s, "bf16") for s in ANY],
+                         ids=lambda v: v if isinstance(v, str) else "%s_to_%s" % v)
+def test_trilinear_any(sizes, dt):
+    check_trilinear(sizes, dt)
