@@ -1096,11 +1096,11 @@ constexpr int kBandLds = kBandXBytes + 2 * 64 * kBandDys;    // 163328
 static_assert(kBandLds <= 160 * 1024, "band LDS");
 }  // namespace
 
-// MODE: 0 W % 8 = 0 (16-byte loads), 1 W % 8 = 4 (the last group of a row
-// holds four voxels: an 8-byte load), 2 any other width (element loads).
+// MODE: 0 W % 8 = 0, 1 other even W (the last group of a row holds fewer than
+// eight voxels), 2 odd W (rows may start in the middle of a 4-byte unit).
 template <int NK, int MODE>
 __global__ __launch_bounds__(512, 1) void conv_band_wgrad(WbArgs a) {
-    constexpr bool PART = MODE == 1, ELEM = MODE == 2;
+    constexpr bool ODDW = MODE == 2;
     constexpr int KT = 27, NTAP = kWgNtap;
     static_assert(NK * 32 <= kBandK, "K steps per band");
     constexpr int DYB = 64 * kBandDys;
@@ -1145,7 +1145,6 @@ __global__ __launch_bounds__(512, 1) void conv_band_wgrad(WbArgs a) {
     if (!consumer) {
         const int XG = (a.hb + 2) * a.Wp / 8;  // 8-voxel groups of one (channel, plane)
         const int YG = a.hb * a.Wp / 8;        // 8-voxel groups of one output channel
-        // PART (W % 8 == 4): the last group of a row holds four voxels (8-byte load)
         auto qdiv = [](int i, uint32_t m) { return (int)(((uint32_t)i * m) >> 20); };
         // The staging index arithmetic is redone at every use (the opaque copy
         // of the thread index keeps it from being hoisted into registers).
@@ -1157,9 +1156,51 @@ __global__ __launch_bounds__(512, 1) void conv_band_wgrad(WbArgs a) {
         // Staging loads are raw buffer loads over one sample's tensor; an
         // offset past the end (padding, idle item) reads zeros, so no load
         // sits behind a branch.
-        // x group: m[0] bits 16..31 = left neighbour, m[1..4] = 8 voxels,
-        // m[5] bits 0..15 = right neighbour (zero at the row ends and past W)
-        auto ld_x = [&](const Step& t, bool live, int ci, int z, int gi, uint32_t* m)
+        // A group's 8 voxels start at byte offset o of the row: one 16-byte load
+        // from the 4-byte unit that holds its first voxel (a row of any width
+        // may start at an odd voxel; the buffer's range is checked 4 bytes at a
+        // time, and a sample's tensor, a multiple of 16 channels, ends at a
+        // 32-byte boundary), with one more unit behind it where rows can be
+        // odd (ODDW).  Raw: m[0] = left neighbour, m[1..4] = units, m[5] = right
+        // neighbour (or, ODDW, the unit behind).  fix_x puts them in place:
+        // m[0] bits 16..31 = left neighbour, m[1..4] = 8 voxels, m[5] bits
+        // 0..15 = right neighbour, zeros past the row's end.  It runs when the
+        // group is written to LDS, so that nothing waits for the loads before.
+        auto ld_raw = [&](__amdgpu_buffer_rsrc_t r, bool ok, uint32_t o, bool lf, bool rt,
+                          uint32_t* m) __attribute__((always_inline)) {
+            const uint32_t b = ok ? (ODDW ? o & ~3u : o) : 0x80000000u;
+            const uint4 v = buf_ld16(r, b, 0);
+            m[1] = v.x; m[2] = v.y; m[3] = v.z; m[4] = v.w;
+            m[0] = buf_ld2(r, ok && lf ? o - 2u : 0x80000000u, 0);
+            m[5] = ODDW ? buf_ld4(r, b + 16u, 0) : buf_ld2(r, ok && rt ? o + 16u : 0x80000000u, 0);
+        };
+        // nv: voxels of the group inside the row; o: any offset with its parity
+        auto fix_units = [&](const uint4& v, uint32_t t, uint32_t o, int nv, uint32_t* w)
+            __attribute__((always_inline)) {
+            if constexpr (ODDW) {
+                const uint32_t sh = (o & 2u) << 3;
+                w[0] = __builtin_amdgcn_alignbit(v.y, v.x, sh);
+                w[1] = __builtin_amdgcn_alignbit(v.z, v.y, sh);
+                w[2] = __builtin_amdgcn_alignbit(v.w, v.z, sh);
+                w[3] = __builtin_amdgcn_alignbit(t, v.w, sh);
+            } else {
+                w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w;
+            }
+            if constexpr (MODE != 0) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int n = nv - 2 * i;
+                    w[i] = n >= 2 ? w[i] : n == 1 ? w[i] & 0xffffu : 0u;
+                }
+            }
+        };
+        auto fix_x = [&](const uint32_t* m, uint32_t o, int nv, bool rt, uint32_t* f)
+            __attribute__((always_inline)) {
+            f[0] = m[0] << 16;
+            fix_units(make_uint4(m[1], m[2], m[3], m[4]), m[5], o, nv, f + 1);
+            f[5] = ODDW ? (rt ? (m[5] >> ((o & 2u) << 3)) & 0xffffu : 0u) : m[5];
+        };
+        auto ld_x = [&](const Step& t, bool live, int ci, int z, int gi, uint32_t* f)
             __attribute__((always_inline)) {
             // the step is wave-uniform; saying so keeps the resource in SGPRs
             const int n = __builtin_amdgcn_readfirstlane(t.n);
@@ -1168,26 +1209,10 @@ __global__ __launch_bounds__(512, 1) void conv_band_wgrad(WbArgs a) {
             const int u = 8 * gi, rr = qdiv(u, a.mWp), col = u - rr * a.Wp;
             const int h = t.h0 - 1 + rr;
             const bool ok = live && (unsigned)z < (unsigned)a.D && (unsigned)h < (unsigned)a.H;
-            const uint32_t o = ok ? (uint32_t)((ci0 + ci) * (uint32_t)V + z * HW + h * a.W + col) * 2u
-                                  : 0x80000000u;
-            if constexpr (ELEM) {
-                uint32_t e[8];
-#pragma unroll
-                for (int j = 0; j < 8; ++j)
-                    e[j] = buf_ld2(xr, ok && col + j < a.W ? o + 2u * j : 0x80000000u, 0);
-                m[1] = e[0] | (e[1] << 16); m[2] = e[2] | (e[3] << 16);
-                m[3] = e[4] | (e[5] << 16); m[4] = e[6] | (e[7] << 16);
-            } else if constexpr (PART) {
-                const bool full = col + 8 <= a.W;
-                const uint4 v = buf_ld16(xr, full ? o : 0x80000000u, 0);
-                const uint2 w = buf_ld8(xr, full ? 0x80000000u : o, 0);
-                m[1] = v.x | w.x; m[2] = v.y | w.y; m[3] = v.z; m[4] = v.w;
-            } else {
-                const uint4 v = buf_ld16(xr, o, 0);
-                m[1] = v.x; m[2] = v.y; m[3] = v.z; m[4] = v.w;
-            }
-            m[0] = buf_ld2(xr, ok && col > 0 ? o - 2u : 0x80000000u, 0) << 16;
-            m[5] = buf_ld2(xr, ok && col + 8 < a.W ? o + 16u : 0x80000000u, 0);
+            const uint32_t o = (uint32_t)((ci0 + ci) * (uint32_t)V + z * HW + h * a.W + col) * 2u;
+            uint32_t m[6];
+            ld_raw(xr, ok, o, col > 0, col + 8 < a.W, m);
+            fix_x(m, o, a.W - col, col + 8 < a.W, f);
         };
         auto st_x = [&](int ci, int z, int gi, const uint32_t* m) __attribute__((always_inline)) {
             unsigned char* base = xs + ci * a.cis + slot_of(z) * a.sls + gi * 16;
@@ -1207,41 +1232,29 @@ __global__ __launch_bounds__(512, 1) void conv_band_wgrad(WbArgs a) {
                 buf_rsrc_u(a.dy + (int64_t)n * a.Co * V, (uint32_t)(a.Co * V * 2));
             const int u = 8 * gi, rr = qdiv(u, a.mWp), col = u - rr * a.Wp;
             const int h = t.h0 + rr;
+            const bool ok = live && h < a.H;
             const uint32_t o =
-                live && h < a.H
-                    ? (uint32_t)((co0 + co) * (uint32_t)V + t.d * HW + h * a.W + col) * 2u
-                    : 0x80000000u;
-            if constexpr (ELEM) {
-                uint32_t e[8];
-#pragma unroll
-                for (int j = 0; j < 8; ++j)
-                    e[j] = buf_ld2(yr, o != 0x80000000u && col + j < a.W ? o + 2u * j : 0x80000000u, 0);
-                return make_uint4(e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16),
-                                  e[6] | (e[7] << 16));
-            }
-            if constexpr (PART) {
-                const bool full = col + 8 <= a.W;
-                uint4 v = buf_ld16(yr, full ? o : 0x80000000u, 0);
-                const uint2 w = buf_ld8(yr, full ? 0x80000000u : o, 0);
-                v.x |= w.x;
-                v.y |= w.y;
-                return v;
-            }
-            return buf_ld16(yr, o, 0);
+                (uint32_t)((co0 + co) * (uint32_t)V + t.d * HW + h * a.W + col) * 2u;
+            const uint32_t b = ok ? (ODDW ? o & ~3u : o) : 0x80000000u;
+            const uint4 v = buf_ld16(yr, b, 0);
+            uint32_t w[4];
+            fix_units(v, ODDW ? buf_ld4(yr, b + 16u, 0) : 0u, o, a.W - col, w);
+            return make_uint4(w[0], w[1], w[2], w[3]);
         };
         constexpr int NXN = (16 * (kBandSlotVox / 8) + 255) / 256;  // x groups per thread, one plane
         constexpr int NDY = 64 * (kBandK / 8) / 256;                // dy groups per thread
-        struct Regs {
+        struct Regs {  // raw loads
             uint32_t m[NXN][6];
             uint4 dy[NDY];
+            uint32_t dt[ODDW ? NDY : 1];
         };
         // A thread's staging items are the same at every step, so their
         // element offsets within a sample (x: at plane 0 of a band starting
         // at row 0; dy: likewise), their LDS offsets and their row / edge
         // flags are computed once; a step adds its wave-uniform plane and band
         // offsets.  Flags: bits 0..15 the item's row in the band, 16 live,
-        // 17 a left neighbour exists, 18 a right neighbour exists, 19 eight
-        // whole voxels (else four).
+        // 17 a left neighbour exists, 18 a right neighbour exists, 20..23 the
+        // voxels inside the row.
         uint32_t xo[NXN], xl[NXN], xf[NXN], yo[NDY], yl[NDY], yf[NDY];
         {
             const int pt = tid - 256;
@@ -1255,8 +1268,7 @@ __global__ __launch_bounds__(512, 1) void conv_band_wgrad(WbArgs a) {
                 xl[q] = (uint32_t)(ci * a.cis + gi * 16);
                 const int nv = a.W - col < 8 ? (a.W - col > 0 ? a.W - col : 0) : 8;
                 xf[q] = (uint32_t)rr | (live ? 1u << 16 : 0u) | (col > 0 ? 1u << 17 : 0u) |
-                        (col + 8 < a.W ? 1u << 18 : 0u) | (col + 8 <= a.W ? 1u << 19 : 0u) |
-                        ((uint32_t)nv << 20);
+                        (col + 8 < a.W ? 1u << 18 : 0u) | ((uint32_t)nv << 20);
             }
 #pragma unroll
             for (int q = 0; q < NDY; ++q) {
@@ -1267,8 +1279,7 @@ __global__ __launch_bounds__(512, 1) void conv_band_wgrad(WbArgs a) {
                 yo[q] = (uint32_t)(co0 + co) * (uint32_t)V + (uint32_t)(rr * a.W + col);
                 yl[q] = (uint32_t)(co * kBandDys + gi * 16);
                 const int nv = a.W - col < 8 ? (a.W - col > 0 ? a.W - col : 0) : 8;
-                yf[q] = (uint32_t)rr | (live ? 1u << 16 : 0u) | (col + 8 <= a.W ? 1u << 19 : 0u) |
-                        ((uint32_t)nv << 20);
+                yf[q] = (uint32_t)rr | (live ? 1u << 16 : 0u) | ((uint32_t)nv << 20);
             }
         }
         // one new plane (d + 1 of step t) and the dy of step t, into registers
@@ -1290,60 +1301,29 @@ __global__ __launch_bounds__(512, 1) void conv_band_wgrad(WbArgs a) {
                 const uint32_t f = xf[q];
                 const int rr = (int)(f & 0xffffu);
                 const bool ok = (f & (1u << 16)) && zok && (unsigned)(rr - 1 + t.h0) < (unsigned)a.H;
-                const uint32_t o = ok ? (xo[q] + xb) * 2u : 0x80000000u;
-                uint32_t* m = R.m[q];
-                if constexpr (ELEM) {
-                    const int nv = (int)((f >> 20) & 15u);
-                    uint32_t e[8];
-#pragma unroll
-                    for (int j = 0; j < 8; ++j)
-                        e[j] = buf_ld2(xr, ok && j < nv ? o + 2u * j : 0x80000000u, 0);
-                    m[1] = e[0] | (e[1] << 16); m[2] = e[2] | (e[3] << 16);
-                    m[3] = e[4] | (e[5] << 16); m[4] = e[6] | (e[7] << 16);
-                } else if constexpr (PART) {
-                    const bool full = f & (1u << 19);
-                    const uint4 v = buf_ld16(xr, full ? o : 0x80000000u, 0);
-                    const uint2 w = buf_ld8(xr, full ? 0x80000000u : o, 0);
-                    m[1] = v.x | w.x; m[2] = v.y | w.y; m[3] = v.z; m[4] = v.w;
-                } else {
-                    const uint4 v = buf_ld16(xr, o, 0);
-                    m[1] = v.x; m[2] = v.y; m[3] = v.z; m[4] = v.w;
-                }
-                m[0] = buf_ld2(xr, ok && (f & (1u << 17)) ? o - 2u : 0x80000000u, 0) << 16;
-                m[5] = buf_ld2(xr, ok && (f & (1u << 18)) ? o + 16u : 0x80000000u, 0);
+                ld_raw(xr, ok, (xo[q] + xb) * 2u, f & (1u << 17), f & (1u << 18), R.m[q]);
             }
 #pragma unroll
             for (int q = 0; q < NDY; ++q) {
                 const uint32_t f = yf[q];
                 const int rr = (int)(f & 0xffffu);
                 const bool ok = (f & (1u << 16)) && rr < hy;
-                const uint32_t o = ok ? (yo[q] + yb) * 2u : 0x80000000u;
-                if constexpr (ELEM) {
-                    const int nv = (int)((f >> 20) & 15u);
-                    uint32_t e[8];
-#pragma unroll
-                    for (int j = 0; j < 8; ++j)
-                        e[j] = buf_ld2(yr, ok && j < nv ? o + 2u * j : 0x80000000u, 0);
-                    R.dy[q] = make_uint4(e[0] | (e[1] << 16), e[2] | (e[3] << 16),
-                                         e[4] | (e[5] << 16), e[6] | (e[7] << 16));
-                } else if constexpr (PART) {
-                    const bool full = f & (1u << 19);
-                    uint4 v = buf_ld16(yr, full ? o : 0x80000000u, 0);
-                    const uint2 w = buf_ld8(yr, full ? 0x80000000u : o, 0);
-                    v.x |= w.x;
-                    v.y |= w.y;
-                    R.dy[q] = v;
-                } else {
-                    R.dy[q] = buf_ld16(yr, o, 0);
-                }
+                const uint32_t o = (yo[q] + yb) * 2u;
+                const uint32_t b = ok ? (ODDW ? o & ~3u : o) : 0x80000000u;
+                R.dy[q] = buf_ld16(yr, b, 0);
+                if constexpr (ODDW) R.dt[q] = buf_ld4(yr, b + 16u, 0);
             }
         };
         auto commit = [&](const Step& t, const Regs& R, unsigned char* db) __attribute__((always_inline)) {
             unsigned char* xb = xs + slot_of(t.d + 1) * a.sls;
+            const uint32_t xe = (uint32_t)((t.d + 1) * HW) + (uint32_t)((t.h0 - 1) * a.W);
+            const uint32_t ye = (uint32_t)(t.d * HW) + (uint32_t)(t.h0 * a.W);
 #pragma unroll
             for (int q = 0; q < NXN; ++q) {
-                if (!(xf[q] & (1u << 16))) continue;
-                const uint32_t* m = R.m[q];
+                const uint32_t f = xf[q];
+                if (!(f & (1u << 16))) continue;
+                uint32_t m[6];
+                fix_x(R.m[q], (xo[q] + xe) * 2u, (int)((f >> 20) & 15u), f & (1u << 18), m);
                 unsigned char* base = xb + xl[q];
                 uint32_t s0[4], s2[4];
 #pragma unroll
@@ -1357,7 +1337,12 @@ __global__ __launch_bounds__(512, 1) void conv_band_wgrad(WbArgs a) {
             }
 #pragma unroll
             for (int q = 0; q < NDY; ++q)
-                if (yf[q] & (1u << 16)) *reinterpret_cast<uint4*>(db + yl[q]) = R.dy[q];
+                if (yf[q] & (1u << 16)) {
+                    uint32_t w[4];
+                    fix_units(R.dy[q], ODDW ? R.dt[q] : 0u, (yo[q] + ye) * 2u,
+                              (int)((yf[q] >> 20) & 15u), w);
+                    *reinterpret_cast<uint4*>(db + yl[q]) = make_uint4(w[0], w[1], w[2], w[3]);
+                }
         };
         // first step of a range or band: planes d - 1 .. d + 1 and dy, synchronously
         auto stage_full = [&](const Step& t, unsigned char* db) __attribute__((always_inline)) {
@@ -1782,13 +1767,12 @@ rat3d_status conv_wgrad_brick(const ConvGeom& g, const void* x, const void* dy, 
         a.mXG = magic(XG);
         a.m3XG = magic(3 * XG);
         a.mYG = magic(YG);
-        // staging mode: whole 8-voxel groups, a half-filled last group, or
-        // element loads (widths that are not a multiple of 4)
-        const int mode = (g.W & 7) == 0 ? 0 : ((g.W & 3) == 0 ? 1 : 2);
+        // staging mode: whole 8-voxel groups, a part-filled last group, odd rows
+        const int mode = (g.W & 7) == 0 ? 0 : ((g.W & 1) == 0 ? 1 : 2);
         char tag[48];
         snprintf(tag, sizeof tag, "conv_band3_wgrad%s%s",
                  bc.nk == 6 ? "" : bc.nk == 4 ? "_k128" : bc.nk == 2 ? "_k64" : "_k32",
-                 mode == 1 ? "_w4" : mode == 2 ? "_elem" : "");
+                 mode == 1 ? "_even" : mode == 2 ? "_odd" : "");
         ProfScope ps(tag, st, conv_flops(g), conv_bytes(g, 2));
         const unsigned grid = (unsigned)((int64_t)Rreal * cigs * cogs);
 #define RAT3D_BAND(NK)                                                           \
