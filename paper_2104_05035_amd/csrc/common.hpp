@@ -93,6 +93,10 @@ __device__ __forceinline__ uint32_t buf_ld2(__amdgpu_buffer_rsrc_t r, uint32_t v
                                             uint32_t soff) {
     return (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(r, voff, soff, 0);
 }
+__device__ __forceinline__ void buf_st4(__amdgpu_buffer_rsrc_t r, uint32_t v, uint32_t voff,
+                                        uint32_t soff) {
+    __builtin_amdgcn_raw_buffer_store_b32(v, r, voff, soff, 0);
+}
 __device__ __forceinline__ void buf_st8(__amdgpu_buffer_rsrc_t r, uint2 v, uint32_t voff,
                                         uint32_t soff) {
     const u32x2 w = {v.x, v.y};

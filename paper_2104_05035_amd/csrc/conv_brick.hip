@@ -46,6 +46,12 @@ union F16B {
 };
 
 constexpr int kBD = 4, kBH = 8, kBW = 16;     // forward output tile
+// Rows this narrow are staged by elements: most of a group's 16-byte loads
+// would fall outside the map.  8 x 256 -> 256, forward, groups against
+// elements: 3x4x3 32.4 and 30.0 us, 5x5x5 45.0 and 42.7 (4 x 64 at 40x40x5:
+// 38.3 and 39.7), 4x4x4 30.8 and 30.9, 6x6x6 42.5 and 45.9, 7x7x7 50.2 and
+// 51.9 (8 x 64 at 7x7x7: 20.4 and 19.8).
+__device__ __forceinline__ bool elem_rows(int W) { return W < 4 || W == 5; }
 constexpr int kWH = 8, kWW = 16;              // weight-gradient voxel brick (one depth slice)
 
 __device__ __forceinline__ f32x4 mfma(const F16B& a, const F16B& b, f32x4 c) {
@@ -183,7 +189,7 @@ __device__ __forceinline__ void lds_barrier() {
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-template <int KS, int NT, int RD, bool ACC, bool DG>
+template <int KS, int NT, int RD, bool ACC, bool DG, bool W8>
 __global__ __launch_bounds__(512, 1) void conv_brick_fd(FdArgs a) {
     constexpr int P = (KS - 1) / 2;
     constexpr int PD = kBD + KS - 1, PH = kBH + KS - 1, PW = kBW + KS - 1;
@@ -322,8 +328,97 @@ __global__ __launch_bounds__(512, 1) void conv_brick_fd(FdArgs a) {
             }
         }
     };
-    // Widths that are not a multiple of 8: item = (channel group, brick
-    // voxel), voxel fastest, loaded and written in one pass.
+    // Other widths: the same items.  A row's 8 columns start anywhere, so a
+    // load covers them from the 4-byte unit of the first (buffer ranges are
+    // checked 4 bytes at a time, and a sample's tensor, a multiple of 32
+    // channels, ends at a 64-byte boundary); where rows can be odd it takes
+    // the unit behind as well and shifts, by the parity of the element's
+    // offset, when the brick is written.  Columns past the width are zeroed.
+    // Before, every brick voxel took eight 2-byte loads, waited for on the
+    // spot, and the results left the consumer waves as 2-byte stores; even
+    // widths now also drain their results in 16-byte units.  Forward, before ->
+    // after: 4 x 64 -> 64 at 46x55x46 154.7 -> 104.1 us (989 TF), 8 x 64 at
+    // 22x26x22 72.2 -> 51.9, 8 x 128 at 12x14x12 44.7 -> 36.5; odd widths, whose
+    // stores are still by elements, 45x55x45 144.7 -> 140.9.  Widths of whole
+    // groups keep kernels of their own (W8): sharing one cost them 4 % of the
+    // input gradient at 16 x 64, 48x56x48 (395 against 380 us).
+    const bool oddw = (a.W & 1) != 0;
+    struct AnyRegs {
+        uint4 v[8];
+        uint32_t t[8];
+    };
+    auto any_item = [&](const Tile& T, int r, int& row, int& cg, int& wg, int& q, uint32_t& vo) {
+        int pair = 0;
+        q = 0;
+        const bool live = r < NRND && item_of(r, pair, q);
+        cg = pair / (PD * PH);
+        row = pair - cg * (PD * PH);
+        const int dd = row / PH, hh = row - dd * PH;
+        const int d = T.d0 - P + dd, h = T.h0 - P + hh;
+        wg = T.w0 + 8 * (q + Q0);
+        const bool ok = live && (unsigned)d < (unsigned)a.D && (unsigned)h < (unsigned)a.H &&
+                        (unsigned)wg < (unsigned)a.W;
+        vo = ok ? (uint32_t)((cg * 8 * V + d * HW + h * a.W + wg) * 2) : 0x80000000u;
+        return live;
+    };
+    auto any_load = [&](int k, AnyRegs& R, int r) {
+        const Tile T = tile_of(k);
+        const int c0 = chunk_c0(T, k);
+        const __amdgpu_buffer_rsrc_t src_r =
+            buf_rsrc_u(a.src + (int64_t)T.n * a.Cs * V, (uint32_t)a.Cs * Vb);
+        int row, cg, wg, q;
+        uint32_t vo;
+        any_item(T, r, row, cg, wg, q, vo);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const uint32_t so = (uint32_t)(c0 + j) * Vb;
+            const uint32_t b = vo == 0x80000000u ? vo : (vo + (so & 2u)) & ~3u;
+            R.v[j] = buf_ld16(src_r, b, so & ~3u);
+            if (oddw) R.t[j] = buf_ld4(src_r, b + 16u, so & ~3u);
+        }
+    };
+    auto any_write = [&](int k, unsigned char* buf, const AnyRegs& R, int r) {
+        const Tile T = tile_of(k);
+        const int c0 = chunk_c0(T, k);
+        int row, cg, wg, q;
+        uint32_t vo;
+        if (!any_item(T, r, row, cg, wg, q, vo)) return;
+        uint4 v[8];
+        const int nv = a.W - wg;  // columns of the group inside the map (from 8 on: all)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            v[j] = R.v[j];
+            if (oddw) {
+                const uint32_t sh = ((vo + (uint32_t)(c0 + j) * Vb) & 2u) << 3;
+                v[j].x = __builtin_amdgcn_alignbit(R.v[j].y, R.v[j].x, sh);
+                v[j].y = __builtin_amdgcn_alignbit(R.v[j].z, R.v[j].y, sh);
+                v[j].z = __builtin_amdgcn_alignbit(R.v[j].w, R.v[j].z, sh);
+                v[j].w = __builtin_amdgcn_alignbit(R.t[j], R.v[j].w, sh);
+            }
+        }
+        unsigned char* rb = buf + (uint32_t)row * RS;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int ww = 8 * (q + Q0) + e + P;  // brick column
+            if (ww < 0 || ww >= PW) continue;
+            const bool in = e < nv;
+            uint32_t o[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const int wd = e >> 1;
+                const uint4 &l = v[2 * c], &h = v[2 * c + 1];
+                const uint32_t wl = wd == 0 ? l.x : wd == 1 ? l.y : wd == 2 ? l.z : l.w;
+                const uint32_t wh = wd == 0 ? h.x : wd == 1 ? h.y : wd == 2 ? h.z : h.w;
+                const uint32_t p = (e & 1) ? pack_hi(wl, wh) : pack_lo(wl, wh);
+                o[c] = in ? p : 0u;
+            }
+            *reinterpret_cast<uint4*>(rb + brick_slot_off<KS>(ww, cg)) =
+                make_uint4(o[0], o[1], o[2], o[3]);
+        }
+    };
+
+    // The narrowest rows (elem_rows): item = (channel group, brick voxel),
+    // voxel fastest, loaded and written in one pass.
     auto stage_generic = [&](int k, unsigned char* buf) {
         const Tile T = tile_of(k);
         const int c0 = chunk_c0(T, k);
@@ -459,14 +554,17 @@ __global__ __launch_bounds__(512, 1) void conv_brick_fd(FdArgs a) {
     // and add them before the single rounding; the producers' stores stay
     // plain bf16 stores.
     const bool split_out = a.nsplit > 1;
-    const bool staged_epi = !split_out && (!ACC || KS == 3) && (a.W & 7) == 0;
+    // (drained by the owners of the group items, so not with element staging)
+    const bool elem = !W8 && elem_rows(a.W);
+    const bool staged_epi = !split_out && (!ACC || KS == 3) &&
+                            (W8 || (KS == 3 && (a.W & 1) == 0 && !elem));
     using OldV = uint2[ACC ? NR : 1][ACC ? CT : 1];
     auto load_old = [&](int k, OldV& o) {
         const Tile T = tile_of(k);
         const __amdgpu_buffer_rsrc_t dst_r = dst_rsrc(T);
         const int w = T.w0 + 4 * kg;
-        // lanes past the width read zeros (offset past the buffer end); the
-        // producers never store those units
+        // lanes past the width read zeros (offset past the buffer end), lanes
+        // across it the next row's values; the producers never store those
         const uint32_t lo =
             w < a.W ? (uint32_t)(((T.co0 + wc * CT * 16 + li) * V + w) * 2) : 0x80000000u;
 #pragma unroll
@@ -542,7 +640,8 @@ __global__ __launch_bounds__(512, 1) void conv_brick_fd(FdArgs a) {
         }
     };
     // The units of staging item r: LDS offsets read into v, global byte
-    // offsets (within sample T.n) into go; units outside the tile's valid
+    // offsets (within sample T.n, a multiple of 4) into go, bit 0 set for a
+    // unit that reaches past the row's end; units outside the tile's valid
     // range get go = 0x80000000 and are not stored.  The eight LDS reads of an
     // item are issued together.
     auto unit_read = [&](const Tile& T, const unsigned char* buf, int r, uint4 (&v)[8],
@@ -568,7 +667,8 @@ __global__ __launch_bounds__(512, 1) void conv_brick_fd(FdArgs a) {
             const int dd = T.d0 + d, hh = T.h0 + h, w = T.w0 + 8 * half;
             const bool ok = live && cg < NT && col >= 0 && col < PW &&
                             !(col == PW - 1 && row >= 4) && dd < a.D && hh < a.H && w < a.W;
-            go[e] = ok ? (uint32_t)(((T.co0 + cg * 16 + li_o) * V + dd * HW + hh * a.W + w) * 2)
+            go[e] = ok ? (uint32_t)(((T.co0 + cg * 16 + li_o) * V + dd * HW + hh * a.W + w) * 2) |
+                             (!W8 && w + 8 > a.W ? 1u : 0u)
                        : 0x80000000u;
             const uint32_t lo = ok ? (uint32_t)row * RS + brick_slot_off<KS>(col, cg) : 0u;
             v[e] = *reinterpret_cast<const uint4*>(buf + lo);
@@ -576,8 +676,17 @@ __global__ __launch_bounds__(512, 1) void conv_brick_fd(FdArgs a) {
     };
     auto unit_store = [&](__amdgpu_buffer_rsrc_t dst_r, const uint4 (&v)[8], const uint32_t (&go)[8]) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e)
-            if (go[e] != 0x80000000u) buf_st16(dst_r, v[e], go[e], 0u);
+        for (int e = 0; e < 8; ++e) {
+            if (go[e] == 0x80000000u) continue;
+            if (W8 || !(go[e] & 1u)) {
+                buf_st16(dst_r, v[e], go[e], 0u);
+            } else {  // the end of a row: W % 8 voxels (an even number)
+                const uint32_t o = go[e] & ~1u;
+                buf_st4(dst_r, v[e].x, o, 0u);
+                if ((a.W & 7) > 2) buf_st4(dst_r, v[e].y, o + 4u, 0u);
+                if ((a.W & 7) > 4) buf_st4(dst_r, v[e].z, o + 8u, 0u);
+            }
+        }
     };
     auto drain_items = [&](const Tile& T, const unsigned char* buf, int r0, int r1) {
         const __amdgpu_buffer_rsrc_t dst_r = dst_rsrc(T);
@@ -634,7 +743,7 @@ __global__ __launch_bounds__(512, 1) void conv_brick_fd(FdArgs a) {
             __builtin_amdgcn_sched_barrier(0);
         }
     };
-    // direct epilogue (widths not a multiple of 8, accumulating 1^3):
+    // direct epilogue (odd widths; 1^3: accumulating or not a multiple of 8):
     // lane holds 4 consecutive w of one output channel per tile row
     auto direct_outputs = [&](int k) {
         const Tile T = tile_of(k);
@@ -702,17 +811,27 @@ __global__ __launch_bounds__(512, 1) void conv_brick_fd(FdArgs a) {
             }
         }
     } else {
-        const bool aligned = (a.W & 7) == 0;
         auto stage_all = [&](int k, unsigned char* buf) {
-            if (!aligned) {
-                stage_generic(k, buf);
-                return;
-            }
+            if constexpr (!W8) {
+                if (elem) {
+                    stage_generic(k, buf);
+                    return;
+                }
 #pragma unroll 1
-            for (int i0 = 0; i0 < NRND; i0 += 2) {
-                uint4 v[2][8];
-                stage_load(k, v, i0);
-                stage_write(buf, v, i0);
+                for (int i0 = 0; i0 < NRND; i0 += 2) {
+                    AnyRegs r0, r1;
+                    any_load(k, r0, i0);
+                    any_load(k, r1, i0 + 1);
+                    any_write(k, buf, r0, i0);
+                    any_write(k, buf, r1, i0 + 1);
+                }
+            } else {
+#pragma unroll 1
+                for (int i0 = 0; i0 < NRND; i0 += 2) {
+                    uint4 v[2][8];
+                    stage_load(k, v, i0);
+                    stage_write(buf, v, i0);
+                }
             }
         };
         // bf16 epilogue of 3^3 tiles: a tile's drain is split over two steps.
@@ -1703,23 +1822,29 @@ rat3d_status conv_fd_brick(const ConvGeom& g, bool dgrad, const void* src, const
         tag = tagbuf;
     }
     ProfScope ps(tag, st, conv_flops(g), conv_bytes(g, 2));
-#define RAT3D_FD(K, N, R)                                                          \
-    do {                                                                           \
-        if (dgrad) {                                                               \
-            if (acc) conv_brick_fd<K, N, R, true, true><<<grid, 512, 0, st>>>(a);  \
-            else conv_brick_fd<K, N, R, false, true><<<grid, 512, 0, st>>>(a);     \
-        } else {                                                                   \
-            if (acc) conv_brick_fd<K, N, R, true, false><<<grid, 512, 0, st>>>(a); \
-            else conv_brick_fd<K, N, R, false, false><<<grid, 512, 0, st>>>(a);    \
-        }                                                                          \
+#define RAT3D_FD(K, N, R, W)                                                          \
+    do {                                                                              \
+        if (dgrad) {                                                                  \
+            if (acc) conv_brick_fd<K, N, R, true, true, W><<<grid, 512, 0, st>>>(a);  \
+            else conv_brick_fd<K, N, R, false, true, W><<<grid, 512, 0, st>>>(a);     \
+        } else {                                                                      \
+            if (acc) conv_brick_fd<K, N, R, true, false, W><<<grid, 512, 0, st>>>(a); \
+            else conv_brick_fd<K, N, R, false, false, W><<<grid, 512, 0, st>>>(a);    \
+        }                                                                             \
+    } while (0)
+#define RAT3D_FD_W(K, N, R)                       \
+    do {                                          \
+        if (g.W % 8 == 0) RAT3D_FD(K, N, R, true); \
+        else RAT3D_FD(K, N, R, false);            \
     } while (0)
     if (g.k == 3) {
-        if (nt == 4) RAT3D_FD(3, 4, 2);
-        else RAT3D_FD(3, 2, 1);
+        if (nt == 4) RAT3D_FD_W(3, 4, 2);
+        else RAT3D_FD_W(3, 2, 1);
     } else {
-        if (nt == 4) RAT3D_FD(1, 4, 2);
-        else RAT3D_FD(1, 2, 1);
+        if (nt == 4) RAT3D_FD_W(1, 4, 2);
+        else RAT3D_FD_W(1, 2, 1);
     }
+#undef RAT3D_FD_W
 #undef RAT3D_FD
     RAT3D_LAUNCH_CHECK();
     if (plan.nsplit > 1) {
