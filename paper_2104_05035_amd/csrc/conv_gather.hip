@@ -216,15 +216,71 @@ __global__ __launch_bounds__(256) void conv_gather_fd(ConvGeom g, const T* __res
             }
 }
 
+// A thread's operands of one K step as they were loaded: eight 2-byte values
+// each (or, forward weights, four words in b).  They are packed when they are
+// written to LDS; packing at the load would wait for it there.
+struct PipeOps {
+    uint32_t a[8], b[8];
+};
+__device__ __forceinline__ uint4 pack8(const uint32_t (&v)[8]) {
+    return make_uint4(v[0] | v[1] << 16, v[2] | v[3] << 16, v[4] | v[5] << 16, v[6] | v[7] << 16);
+}
+// S K steps, the loads two steps ahead of their multiplication (the grids of
+// strided maps leave a CU two workgroups or so: too few waves to hide a load
+// behind one step).  load(st, R) issues step st's loads, stage(st, R) writes
+// them to LDS buffer st & 1, mul(st) multiplies from it.  No load sits behind a
+// branch inside the loop, where it would be waited for at the branch's end.
+// Every thread passes the same barriers.
+template <class L, class G, class M>
+__device__ __forceinline__ void pipe_steps(int S, L&& load, G&& stage, M&& mul) {
+    __syncthreads();  // tables the loads read
+    if (S <= 0) return;
+    PipeOps R0, R1;
+    load(0, R0);
+    if (S > 1) load(1, R1);
+    stage(0, R0);
+    __syncthreads();
+    int st = 0;
+    for (; st + 3 < S; st += 2) {
+        load(st + 2, R0);
+        mul(st);
+        stage(st + 1, R1);
+        __syncthreads();
+        load(st + 3, R1);
+        mul(st + 1);
+        stage(st + 2, R0);
+        __syncthreads();
+    }
+    const int left = S - st;  // 1, 2 or 3
+    if (left == 3) load(st + 2, R0);
+    mul(st);
+    if (left >= 2) {
+        stage(st + 1, R1);
+        __syncthreads();
+        mul(st + 1);
+    }
+    if (left == 3) {
+        stage(st + 2, R0);
+        __syncthreads();
+        mul(st + 2);
+    }
+}
+
 // Forward, bfloat16, source channels a multiple of 32 (every K step of 32
-// is whole): the same 64 x 64 tiles, pipelined.  The next K step's operands
-// are loaded into registers (unconditionally: taps outside the volume read
-// element 0 and are zeroed) while the current step multiplies from one of
-// two LDS buffers, so a step costs one barrier and no exposed load latency.
-// A thread's 8 K values are consecutive taps of one or two channels: the
-// channel and tap of the first come from one division, the rest by stepping
-// the tap with a wrap; a tap's (kd, kh, kw) come from a table in LDS.
+// is whole): the same 64 x 64 tiles and the same order of sums, pipelined by
+// pipe_steps through two LDS buffers.  A thread's 8 K values are consecutive
+// taps of one or two channels: the channel and tap of the first come from one
+// division, the rest by stepping the tap with a wrap.  A tap's offset and its
+// coordinates as bits come from a table in LDS; a row knows which coordinates
+// are outside the volume for it, so a tap costs one test, one addition and a
+// buffer load that reads zero when it is outside (WIDE, for tensors of 2 GiB
+// and more: 64-bit addresses).  Bound by the latency of those 2-byte loads.
+// With the offset in 64-bit arithmetic per element and the loads one step
+// ahead, packed at once: 8 x 64 -> 128 at 24x28x24, stride 2, 96.7 us, now
+// 65.4; 8 x 128 -> 256 at 12x14x12 159.6 -> 109.4; 4 x 64 -> 128 at 46x55x46
+// 238.7 -> 154.0.
 constexpr int kGatherMaxTaps = 343;
+template <bool WIDE>
 __global__ __launch_bounds__(256) void conv_gather_fwd_pipe(ConvGeom g, const bf16* __restrict__ src,
                                                             const bf16* __restrict__ wt,
                                                             const float* __restrict__ bias,
@@ -232,7 +288,8 @@ __global__ __launch_bounds__(256) void conv_gather_fwd_pipe(ConvGeom g, const bf
     constexpr int KV = 8, BK = 32;
     __shared__ __align__(16) unsigned char As[2][64 * kRow];
     __shared__ __align__(16) unsigned char Bs[2][64 * kRow];
-    __shared__ int taps[kGatherMaxTaps];  // kd | kh << 8 | kw << 16
+    // a tap's element offset, and its bits kd | 8 + kh | 16 + kw
+    __shared__ int2 taps[kGatherMaxTaps];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave & 1, wn = wave >> 1;
@@ -243,59 +300,67 @@ __global__ __launch_bounds__(256) void conv_gather_fwd_pipe(ConvGeom g, const bf
     const int c0 = blockIdx.y * 64;
     for (int t = tid; t < KT; t += 256) {
         const int kd = t / (g.k * g.k), r = t - kd * g.k * g.k, kh = r / g.k;
-        taps[t] = kd | kh << 8 | (r - kh * g.k) << 16;
+        const int kw = r - kh * g.k;
+        taps[t] = make_int2((int)(((int64_t)kd * g.H + kh) * g.W + kw),
+                            1 << kd | 256 << kh | 65536 << kw);
     }
 
     // this thread's A row (an output voxel) and B row (an output channel)
     const int ar = tid >> 2, aq = tid & 3;
     const int64_t am = m0 + ar;
     const bool arow_ok = am < M;
-    int id0 = 0, ih0 = 0, iw0 = 0;
-    int64_t a_base = 0;
-    {
-        const int64_t mm = arow_ok ? am : 0;
-        const int64_t n = mm / Vrow;
-        int64_t sp = mm - n * Vrow;
+    int64_t a_base = 0;  // element of tap 0 of channel 0 (may lie before the row)
+    uint32_t a_out = ~0u;  // bit set: that tap coordinate is outside the volume
+    if (arow_ok) {
+        const int64_t n = am / Vrow;
+        int64_t sp = am - n * Vrow;
         const int od = (int)(sp / ((int64_t)g.Ho * g.Wo));
         sp -= (int64_t)od * g.Ho * g.Wo;
         const int oh = (int)(sp / g.Wo), ow = (int)(sp - (int64_t)oh * g.Wo);
-        id0 = od * g.s - g.p;
-        ih0 = oh * g.s - g.p;
-        iw0 = ow * g.s - g.p;
-        a_base = n * g.Ci * Vsrc;
+        const int id0 = od * g.s - g.p, ih0 = oh * g.s - g.p, iw0 = ow * g.s - g.p;
+        a_base = n * g.Ci * Vsrc + ((int64_t)id0 * g.H + ih0) * g.W + iw0;
+        for (int q = 0; q < g.k; ++q) {
+            if ((unsigned)(id0 + q) < (unsigned)g.D) a_out &= ~(1u << q);
+            if ((unsigned)(ih0 + q) < (unsigned)g.H) a_out &= ~(256u << q);
+            if ((unsigned)(iw0 + q) < (unsigned)g.W) a_out &= ~(65536u << q);
+        }
     }
+    const __amdgpu_buffer_rsrc_t src_r =
+        buf_rsrc(src, WIDE ? 0u : (uint32_t)(2 * g.N * g.Ci * (int)Vsrc));
     const int bcol = c0 + (tid >> 2);
     const bool bcol_ok = bcol < g.Co;
     const bf16* wrow = wt + (int64_t)(bcol_ok ? bcol : 0) * K;
 
-    uint32_t av[KV / 2];
-    uint4 bv;
-    auto load = [&](int k0) {
-        const int kf = k0 + aq * KV;
-        int c = kf / KT, t = kf - c * KT;
-        bf16 v[KV];
+    auto load = [&](int st, PipeOps& R) {
+        const int k0 = st * BK, kf = k0 + aq * KV;
+        const int c = kf / KT;
+        int t = kf - c * KT;
+        int64_t base = a_base + c * Vsrc;
+        uint32_t base32 = (uint32_t)base * 2u;
 #pragma unroll
         for (int j = 0; j < KV; ++j) {
-            const int e = taps[t];
-            const int id = id0 + (e & 0xff), ih = ih0 + ((e >> 8) & 0xff), iw = iw0 + (e >> 16);
-            const bool ok = arow_ok && (unsigned)id < (unsigned)g.D &&
-                            (unsigned)ih < (unsigned)g.H && (unsigned)iw < (unsigned)g.W;
-            const int64_t off = ok ? a_base + c * Vsrc + ((int64_t)id * g.H + ih) * g.W + iw : 0;
-            const bf16 x = src[off];
-            v[j] = ok ? x : (bf16)0;
+            const int2 e = taps[t];
+            const bool ok = (a_out & (uint32_t)e.y) == 0;
+            if constexpr (WIDE) {
+                const bf16 x = src[ok ? base + e.x : 0];
+                R.a[j] = ok ? x : (bf16)0;
+            } else {
+                R.a[j] = buf_ld2(src_r, ok ? base32 + 2u * (uint32_t)e.x : 0x80000000u, 0u);
+            }
             if (++t == KT) {
                 t = 0;
-                ++c;
+                base += Vsrc;
+                base32 += 2u * (uint32_t)Vsrc;
             }
         }
-#pragma unroll
-        for (int j = 0; j < KV / 2; ++j) av[j] = (uint32_t)v[2 * j] | (uint32_t)v[2 * j + 1] << 16;
-        const uint4 w4 = *reinterpret_cast<const uint4*>(wrow + k0 + aq * KV);
-        bv = bcol_ok ? w4 : make_uint4(0u, 0u, 0u, 0u);
+        const uint4 u = *reinterpret_cast<const uint4*>(wrow + k0 + aq * KV);
+        R.b[0] = u.x; R.b[1] = u.y; R.b[2] = u.z; R.b[3] = u.w;
     };
-    auto stage = [&](int buf) {
-        *reinterpret_cast<uint4*>(As[buf] + ar * kRow + aq * 16) = make_uint4(av[0], av[1], av[2], av[3]);
-        *reinterpret_cast<uint4*>(Bs[buf] + (tid >> 2) * kRow + aq * 16) = bv;
+    auto stage = [&](int st, const PipeOps& R) {
+        const int buf = st & 1;
+        *reinterpret_cast<uint4*>(As[buf] + ar * kRow + aq * 16) = pack8(R.a);
+        *reinterpret_cast<uint4*>(Bs[buf] + (tid >> 2) * kRow + aq * 16) =
+            bcol_ok ? make_uint4(R.b[0], R.b[1], R.b[2], R.b[3]) : make_uint4(0u, 0u, 0u, 0u);
     };
 
     f32x4 acc[2][2];
@@ -304,18 +369,10 @@ __global__ __launch_bounds__(256) void conv_gather_fwd_pipe(ConvGeom g, const bf
 #pragma unroll
         for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    __syncthreads();  // the tap table
     const int S = K / BK;
-    load(0);
-    stage(0);
-    __syncthreads();
-    for (int st = 0; st < S; ++st) {
-        const bool more = st + 1 < S;
-        if (more) load((st + 1) * BK);
+    pipe_steps(S, load, stage, [&](int st) {
         tile_mma<bf16>(As[st & 1], Bs[st & 1], acc, lane, wm, wn);
-        if (more) stage((st + 1) & 1);
-        __syncthreads();
-    }
+    });
 
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -483,12 +540,13 @@ __global__ __launch_bounds__(256) void conv_gather_dgrad_phase(ConvGeom g,
 }
 
 // The strided input gradient in bf16 with C_out (the channels its K runs
-// over) a multiple of 32, pipelined like conv_gather_fwd_pipe: the
-// class's taps (at most (k / s + 1)^3) in an LDS table built once, each
-// thread's 8 consecutive K values (co, tap) stepped through it, the next K
-// step's loads issued unconditionally before the current step's MFMAs into
-// the other of two LDS buffers.
+// over) a multiple of 32, pipelined like conv_gather_fwd_pipe: the class's
+// taps (at most (k / s + 1)^3) in an LDS table built once, each thread's 8
+// consecutive K values (co, tap) stepped through it.  Weights are 2-byte loads
+// too (a class's taps are not adjacent).  Before -> after, shapes as there:
+// 144.5 -> 130.8 us, 119.8 -> 86.9, 442.5 -> 426.5.
 constexpr int kPhaseMaxTaps = 64;
+template <bool WIDE>
 __global__ __launch_bounds__(256) void conv_gather_dgrad_phase_pipe(ConvGeom g,
                                                                     const bf16* __restrict__ dy,
                                                                     const bf16* __restrict__ wt,
@@ -497,8 +555,9 @@ __global__ __launch_bounds__(256) void conv_gather_dgrad_phase_pipe(ConvGeom g,
     constexpr int KV = 8, BK = 32;
     __shared__ __align__(16) unsigned char As[2][64 * kRow];
     __shared__ __align__(16) unsigned char Bs[2][64 * kRow];
-    __shared__ int toff[kPhaseMaxTaps];  // od | oh << 8 | ow << 16 offsets (each + 128)
-    __shared__ int tflat[kPhaseMaxTaps]; // flattened tap kd * k^2 + kh * k + kw
+    // a tap's dy element offset, bits jd | 8 + jh | 16 + jw, flattened weight
+    // tap kd * k^2 + kh * k + kw
+    __shared__ int4 taps[kPhaseMaxTaps];
 
     const int s = g.s;
     const int cls = blockIdx.z;
@@ -526,59 +585,70 @@ __global__ __launch_bounds__(256) void conv_gather_dgrad_phase_pipe(ConvGeom g,
     for (int j = tid; j < KTc; j += 256) {
         const int jd = j / (nh * nw), r = j - jd * nh * nw, jh = r / nw, jw = r - jh * nw;
         const int td = t0d + s * jd, th = t0h + s * jh, tw = t0w + s * jw;
-        toff[j] = ((rd + g.p - td) / s + 128) | ((rh + g.p - th) / s + 128) << 8 |
-                  ((rw + g.p - tw) / s + 128) << 16;
-        tflat[j] = (td * g.k + th) * g.k + tw;
+        const int64_t off = ((int64_t)((rd + g.p - td) / s) * g.Ho + (rh + g.p - th) / s) * g.Wo +
+                            (rw + g.p - tw) / s;
+        taps[j] = make_int4((int)off, 1 << jd | 256 << jh | 65536 << jw,
+                            (td * g.k + th) * g.k + tw, 0);
     }
     const int ar = tid >> 2, aq = tid & 3;
     const int64_t am = m0 + ar;
     const bool arow_ok = am < M;
-    int a_d = 0, a_h = 0, a_w = 0;
-    int64_t a_base = 0;
+    int64_t a_base = 0;    // dy element of channel 0 at the row's own index
+    uint32_t a_out = ~0u;  // bit set: that tap of the class is outside dy
     if (arow_ok) {
         const int64_t n = am / Vc;
         int64_t sp = am - n * Vc;
-        a_d = (int)(sp / ((int64_t)Mh * Mw));
+        const int a_d = (int)(sp / ((int64_t)Mh * Mw));
         sp -= (int64_t)a_d * Mh * Mw;
-        a_h = (int)(sp / Mw);
-        a_w = (int)(sp - (int64_t)a_h * Mw);
-        a_base = n * g.Co * Vsrc;
+        const int a_h = (int)(sp / Mw), a_w = (int)(sp - (int64_t)a_h * Mw);
+        a_base = n * g.Co * Vsrc + ((int64_t)a_d * g.Ho + a_h) * g.Wo + a_w;
+        for (int q = 0; q < nd; ++q)
+            if ((unsigned)(a_d + (rd + g.p - t0d - s * q) / s) < (unsigned)g.Do) a_out &= ~(1u << q);
+        for (int q = 0; q < nh; ++q)
+            if ((unsigned)(a_h + (rh + g.p - t0h - s * q) / s) < (unsigned)g.Ho) a_out &= ~(256u << q);
+        for (int q = 0; q < nw; ++q)
+            if ((unsigned)(a_w + (rw + g.p - t0w - s * q) / s) < (unsigned)g.Wo)
+                a_out &= ~(65536u << q);
     }
+    const __amdgpu_buffer_rsrc_t dy_r =
+        buf_rsrc(dy, WIDE ? 0u : (uint32_t)(2 * g.N * g.Co * (int)Vsrc));
+    const __amdgpu_buffer_rsrc_t wt_r = buf_rsrc(wt, WIDE ? 0u : (uint32_t)(2 * g.Co * g.Ci * KT));
     const int bcol = c0 + (tid >> 2);
     const bool bcol_ok = bcol < g.Ci;
     const int bc = bcol_ok ? bcol : 0;
 
-    uint32_t av[KV / 2], bv[KV / 2];
-    auto load = [&](int k0) {
-        const int kf = k0 + aq * KV;
-        int co = kf / KTc, j = kf - co * KTc;
-        bf16 a[KV], b[KV];
+    auto load = [&](int st, PipeOps& R) {
+        const int kf = st * BK + aq * KV;
+        const int co = kf / KTc;
+        int j = kf - co * KTc;
+        int64_t ab = a_base + co * Vsrc, bb = ((int64_t)co * g.Ci + bc) * KT;
+        uint32_t ab32 = (uint32_t)ab * 2u, bb32 = (uint32_t)bb * 2u;
 #pragma unroll
         for (int q = 0; q < KV; ++q) {
-            const int e = toff[j];
-            const int od = a_d + (e & 0xff) - 128, oh = a_h + ((e >> 8) & 0xff) - 128,
-                      ow = a_w + (e >> 16) - 128;
-            const bool ok = arow_ok && (unsigned)od < (unsigned)g.Do &&
-                            (unsigned)oh < (unsigned)g.Ho && (unsigned)ow < (unsigned)g.Wo;
-            const int64_t off = ok ? a_base + co * Vsrc + ((int64_t)od * g.Ho + oh) * g.Wo + ow : 0;
-            const bf16 xa = dy[off];
-            a[q] = ok ? xa : (bf16)0;
-            const bf16 xb = wt[((int64_t)co * g.Ci + bc) * KT + tflat[j]];
-            b[q] = bcol_ok ? xb : (bf16)0;
+            const int4 e = taps[j];
+            const bool ok = (a_out & (uint32_t)e.y) == 0;
+            if constexpr (WIDE) {
+                const bf16 xa = dy[ok ? ab + e.x : 0];
+                R.a[q] = ok ? xa : (bf16)0;
+                const bf16 xb = wt[bb + e.z];
+                R.b[q] = bcol_ok ? xb : (bf16)0;
+            } else {
+                R.a[q] = buf_ld2(dy_r, ok ? ab32 + 2u * (uint32_t)e.x : 0x80000000u, 0u);
+                R.b[q] = buf_ld2(wt_r, bcol_ok ? bb32 + 2u * (uint32_t)e.z : 0x80000000u, 0u);
+            }
             if (++j == KTc) {
                 j = 0;
-                ++co;
+                ab += Vsrc;
+                ab32 += 2u * (uint32_t)Vsrc;
+                bb += (int64_t)g.Ci * KT;
+                bb32 += 2u * (uint32_t)(g.Ci * KT);
             }
         }
-#pragma unroll
-        for (int q = 0; q < KV / 2; ++q) {
-            av[q] = (uint32_t)a[2 * q] | (uint32_t)a[2 * q + 1] << 16;
-            bv[q] = (uint32_t)b[2 * q] | (uint32_t)b[2 * q + 1] << 16;
-        }
     };
-    auto stage = [&](int buf) {
-        *reinterpret_cast<uint4*>(As[buf] + ar * kRow + aq * 16) = make_uint4(av[0], av[1], av[2], av[3]);
-        *reinterpret_cast<uint4*>(Bs[buf] + (tid >> 2) * kRow + aq * 16) = make_uint4(bv[0], bv[1], bv[2], bv[3]);
+    auto stage = [&](int st, const PipeOps& R) {
+        const int buf = st & 1;
+        *reinterpret_cast<uint4*>(As[buf] + ar * kRow + aq * 16) = pack8(R.a);
+        *reinterpret_cast<uint4*>(Bs[buf] + (tid >> 2) * kRow + aq * 16) = pack8(R.b);
     };
 
     f32x4 acc[2][2];
@@ -587,20 +657,10 @@ __global__ __launch_bounds__(256) void conv_gather_dgrad_phase_pipe(ConvGeom g,
 #pragma unroll
         for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    __syncthreads();  // the tap tables
-    const int S = Kc / BK;
-    if (S > 0) {
-        load(0);
-        stage(0);
-    }
-    __syncthreads();
-    for (int st = 0; st < S; ++st) {
-        const bool more = st + 1 < S;
-        if (more) load((st + 1) * BK);
+    const int S = Kc / BK;  // 0: no tap reaches this class
+    pipe_steps(S, load, stage, [&](int st) {
         tile_mma<bf16>(As[st & 1], Bs[st & 1], acc, lane, wm, wn);
-        if (more) stage((st + 1) & 1);
-        __syncthreads();
-    }
+    });
 
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -718,6 +778,106 @@ __global__ __launch_bounds__(256) void conv_gather_wgrad(ConvGeom g, const T* __
         __syncthreads();
         tile_mma<T>(As, Bs, acc, lane, wm, wn);
     }
+
+    float* out = part + (int64_t)blockIdx.z * g.Co * Ncols;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int co = co0 + wm * 32 + i * 16 + 4 * (lane >> 4) + e;
+                const int col = col0 + wn * 32 + j * 16 + (lane & 15);
+                if (co < g.Co && col < Ncols) out[(int64_t)co * Ncols + col] = acc[i][j][e];
+            }
+}
+
+// The same weight gradient in bf16, k <= 7, tensors below 2 GiB, pipelined: a
+// K step's 32 voxels are table entries in LDS (a ring of four, filled two steps
+// ahead), {x element of tap 0, bits of the tap coordinates outside the volume,
+// dy element, 0}, and an operand is a buffer load at entry + column offset.
+// Tiles, K ranges and the order of the sums are those of conv_gather_wgrad,
+// which waits for each step's loads before it multiplies.  It against this,
+// shapes as for conv_gather_fwd_pipe: 121.9 and 113.9 us, 61.8 and 55.2, 433.4
+// and 384.8; stride 1, 8 x 256 -> 256 at 3x4x3 37.1 and 33.4.
+__global__ __launch_bounds__(256) void conv_gather_wgrad_pipe(ConvGeom g, const bf16* __restrict__ x,
+                                                              const bf16* __restrict__ dy,
+                                                              float* __restrict__ part,
+                                                              int kchunk) {
+    constexpr int KV = 8, BK = 32;
+    __shared__ __align__(16) unsigned char As[2][64 * kRow];
+    __shared__ __align__(16) unsigned char Bs[2][64 * kRow];
+    __shared__ int4 vtab[4][BK];
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm = wave & 1, wn = wave >> 1;
+    const int KT = g.k * g.k * g.k;
+    const int Ncols = g.Ci * KT;
+    const int HWo = g.Ho * g.Wo, Vo = g.Do * HWo, Vi = g.D * g.H * g.W;
+    const int Ktot = g.N * Vo;
+    const int kbeg = (int)blockIdx.z * kchunk;
+    const int kend = Ktot - kbeg < kchunk ? Ktot : kbeg + kchunk;
+    const int co0 = blockIdx.x * 64, col0 = blockIdx.y * 64;
+
+    const int row = tid >> 2, aq = tid & 3;
+    const bool a_ok = co0 + row < g.Co, b_ok = col0 + row < Ncols;
+    const uint32_t a_off = (uint32_t)(co0 + row) * (uint32_t)Vo * 2u;
+    uint32_t b_off = 0, b_bits = 0;
+    if (b_ok) {
+        const int ci = (col0 + row) / KT, t = col0 + row - ci * KT;
+        const int kd = t / (g.k * g.k), r = t - kd * g.k * g.k, kh = r / g.k, kw = r - kh * g.k;
+        b_off = 2u * ((uint32_t)ci * (uint32_t)Vi + (uint32_t)((kd * g.H + kh) * g.W + kw));
+        b_bits = 1u << kd | 256u << kh | 65536u << kw;
+    }
+    const __amdgpu_buffer_rsrc_t x_r = buf_rsrc(x, (uint32_t)(2 * g.N * g.Ci * Vi));
+    const __amdgpu_buffer_rsrc_t dy_r = buf_rsrc(dy, (uint32_t)(2 * g.N * g.Co * Vo));
+
+    auto fill = [&](int st) {
+        if (tid >= BK) return;
+        const int v = kbeg + st * BK + tid;
+        int4 e = make_int4(0, -1, -1, 0);
+        if (v < kend) {
+            const int n = v / Vo, o = v - n * Vo, od = o / HWo, r = o - od * HWo;
+            const int oh = r / g.Wo, ow = r - oh * g.Wo;
+            const int id = od * g.s - g.p, ih = oh * g.s - g.p, iw = ow * g.s - g.p;
+            uint32_t out = ~0u;
+            for (int q = 0; q < g.k; ++q) {
+                if ((unsigned)(id + q) < (unsigned)g.D) out &= ~(1u << q);
+                if ((unsigned)(ih + q) < (unsigned)g.H) out &= ~(256u << q);
+                if ((unsigned)(iw + q) < (unsigned)g.W) out &= ~(65536u << q);
+            }
+            e = make_int4((int)(2u * ((uint32_t)(n * g.Ci) * (uint32_t)Vi +
+                                      (uint32_t)((id * g.H + ih) * g.W + iw))),
+                          (int)out, (int)(2u * ((uint32_t)(n * g.Co) * (uint32_t)Vo + (uint32_t)o)),
+                          0);
+        }
+        vtab[st & 3][tid] = e;
+    };
+    auto load = [&](int st, PipeOps& R) {
+#pragma unroll
+        for (int j = 0; j < KV; ++j) {
+            const int4 e = vtab[st & 3][aq * KV + j];
+            R.a[j] = buf_ld2(dy_r, a_ok && e.z != -1 ? (uint32_t)e.z + a_off : 0x80000000u, 0u);
+            R.b[j] = buf_ld2(x_r, b_ok && ((uint32_t)e.y & b_bits) == 0 ? (uint32_t)e.x + b_off
+                                                                      : 0x80000000u, 0u);
+        }
+        fill(st + 2);
+    };
+    auto stage = [&](int st, const PipeOps& R) {
+        *reinterpret_cast<uint4*>(As[st & 1] + row * kRow + aq * 16) = pack8(R.a);
+        *reinterpret_cast<uint4*>(Bs[st & 1] + row * kRow + aq * 16) = pack8(R.b);
+    };
+
+    f32x4 acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    fill(0);
+    fill(1);
+    pipe_steps((kend - kbeg + BK - 1) / BK, load, stage, [&](int st) {
+        tile_mma<bf16>(As[st & 1], Bs[st & 1], acc, lane, wm, wn);
+    });
 
     float* out = part + (int64_t)blockIdx.z * g.Co * Ncols;
 #pragma unroll
@@ -873,6 +1033,16 @@ double conv_bytes(const ConvGeom& g, size_t esz) {
                           (double)g.N * g.Co * g.Do * g.Ho * g.Wo);
 }
 
+// The pipelined kernels address whole tensors with 32-bit byte offsets into a
+// buffer whose out-of-range reads are zero; tensors of 2 GiB and more take
+// 64-bit addresses (WIDE).
+static bool pipe_narrow(const ConvGeom& g) {
+    const int64_t lim = (int64_t)1 << 30;  // 2-byte elements
+    return (int64_t)g.N * g.Ci * g.D * g.H * g.W < lim &&
+           (int64_t)g.N * g.Co * g.Do * g.Ho * g.Wo < lim &&
+           (int64_t)g.Co * g.Ci * g.k * g.k * g.k < lim;
+}
+
 template <typename T>
 static rat3d_status gather_fd(const ConvGeom& g, bool dgrad, const void* src, const void* w,
                               const float* bias, void* dst, int accumulate, hipStream_t st) {
@@ -883,11 +1053,16 @@ static rat3d_status gather_fd(const ConvGeom& g, bool dgrad, const void* src, co
     const int cols = dgrad ? g.Ci : g.Co;
     dim3 grid((unsigned)ceil_div(rows, 64), (unsigned)ceil_div(cols, 64));
     if constexpr (std::is_same<T, bf16>::value) {
-        // (16-byte weight loads: K = Ci k^3 is a multiple of 8, the base must be aligned)
+        // (16-byte weight loads: K = Ci k^3 is a multiple of 8, the base must be aligned;
+        // a tap's offset in 32 bits)
         if (!dgrad && !accumulate && g.Ci % 32 == 0 && g.k * g.k * g.k <= kGatherMaxTaps &&
-            ((uintptr_t)w & 15u) == 0) {
-            conv_gather_fwd_pipe<<<grid, 256, 0, st>>>(g, (const bf16*)src, (const bf16*)w, bias,
-                                                       (bf16*)dst);
+            ((uintptr_t)w & 15u) == 0 && (int64_t)g.k * g.H * g.W < ((int64_t)1 << 31)) {
+            if (pipe_narrow(g))
+                conv_gather_fwd_pipe<false><<<grid, 256, 0, st>>>(g, (const bf16*)src,
+                                                                  (const bf16*)w, bias, (bf16*)dst);
+            else
+                conv_gather_fwd_pipe<true><<<grid, 256, 0, st>>>(g, (const bf16*)src,
+                                                                 (const bf16*)w, bias, (bf16*)dst);
             RAT3D_LAUNCH_CHECK();
             return RAT3D_OK;
         }
@@ -918,11 +1093,16 @@ static rat3d_status gather_dgrad_phase(const ConvGeom& g, const void* dy, const 
     dim3 grid((unsigned)ceil_div(rows, 64), (unsigned)ceil_div(g.Ci, 64),
               (unsigned)(g.s * g.s * g.s));
     if constexpr (std::is_same<T, bf16>::value) {
-        // class tap sets of at most (k / s + 1)^3 taps, offsets within +-127
+        // class tap sets of at most (k / s + 1)^3 taps, a tap's offset in 32 bits
         const int tps = g.k / g.s + 1;
-        if (g.Co % 32 == 0 && tps * tps * tps <= kPhaseMaxTaps && g.k <= 127) {
-            conv_gather_dgrad_phase_pipe<<<grid, 256, 0, st>>>(g, (const bf16*)dy, (const bf16*)w,
-                                                               (bf16*)dx, accumulate);
+        if (g.Co % 32 == 0 && tps * tps * tps <= kPhaseMaxTaps &&
+            (int64_t)g.k * g.Ho * g.Wo < ((int64_t)1 << 31)) {
+            if (pipe_narrow(g))
+                conv_gather_dgrad_phase_pipe<false><<<grid, 256, 0, st>>>(
+                    g, (const bf16*)dy, (const bf16*)w, (bf16*)dx, accumulate);
+            else
+                conv_gather_dgrad_phase_pipe<true><<<grid, 256, 0, st>>>(
+                    g, (const bf16*)dy, (const bf16*)w, (bf16*)dx, accumulate);
             RAT3D_LAUNCH_CHECK();
             return RAT3D_OK;
         }
@@ -955,7 +1135,10 @@ rat3d_status conv_wgrad_gather(const ConvGeom& g, rat3d_dtype dt, const void* x,
     {
     ProfScope ps("conv_gather_wgrad", st, conv_flops(g),
                  conv_bytes(g, dt == RAT3D_BF16 ? 2 : 4));
-    if (dt == RAT3D_BF16)
+    if (dt == RAT3D_BF16 && g.k <= 7 && pipe_narrow(g))
+        conv_gather_wgrad_pipe<<<grid, 256, 0, st>>>(g, (const bf16*)x, (const bf16*)dy, part,
+                                                     (int)kchunk);
+    else if (dt == RAT3D_BF16)
         conv_gather_wgrad<bf16><<<grid, 256, 0, st>>>(g, (const bf16*)x, (const bf16*)dy, part,
                                                       kchunk);
     else
