@@ -1201,7 +1201,7 @@ __global__ __launch_bounds__(512, 1) void conv_brick_wgrad(WgArgs a) {
 }
 
 // ---------------------------------------------------------------- band wgrad
-// Row-band weight gradient for narrow maps (W a multiple of 4, at most 56).
+// Row-band weight gradient for maps of any width up to 56.
 // A step is one output depth plane d of a band of hb whole rows starting at
 // h0, flattened row-major with a row pitch Wp = W rounded up to 8 into the
 // GEMM K index (hb * Wp <= NK * 32; pad columns hold dy = 0), so
@@ -1698,11 +1698,17 @@ static BandCfg band_cfg(const ConvGeom& g) {
     if (Wp > 56 || (int64_t)g.Ci * v2 >= ((int64_t)1 << 31) ||
         (int64_t)g.Co * v2 >= ((int64_t)1 << 31))
         return c;
-    // element-loaded widths (W % 4 != 0) only on maps of 128 voxels or more:
-    // below that the kernel's fixed costs (prologue, one partial block per
-    // workgroup) exceed the gather kernel's time (3x4x3: 47 vs 39 us at 256
-    // channels, measured; 6x7x6: 69 vs 128 us)
-    if (g.W % 4 != 0 && (int64_t)g.D * g.H * g.W < 128) return c;
+    // Small maps of widths that are no multiple of 4: the kernel's fixed costs
+    // (prologue, one partial block per workgroup) against the gather kernel's
+    // time, which grows with volumes, channels and voxels.  Weight gradient,
+    // gather and this, us: 8 x 256 at 3x4x3 33.6 and 38.2, 3x3x3 29.0 and 45.1;
+    // 8 x 128 at 2x6x7 22.2 and 27.9; at 5x5x5, whose rows nearly fill a group,
+    // 16 x 64 18.7 and 24.6, 4 x 128 20.8 and 22.9, 8 x 128 26.1 and 27.6, 1 x 256
+    // 26.5 and 29.8, and from 2^18 on 16 x 128 37.2 and 31.5, 4 x 256 46.9 and
+    // 37.7, 8 x 256 63.3 and 45.0, 16 x 256 100.1 and 60.0 (0.54 to 0.89 of the
+    // gather kernel's time at 4x5x5, 4x5x6, 4x4x7 and 5x4x5 too).
+    const bool pays = g.W >= 5 && g.W <= 7 && g.D >= 4 && (int64_t)g.N * g.Ci * g.Co >= 1 << 18;
+    if (g.W % 4 != 0 && (int64_t)g.D * g.H * g.W < (pays ? 96 : 128)) return c;
     int64_t best = -1;
     // least work per plane: each band costs its nk K steps plus a fixed
     // overhead of about two (barrier, staging of hb + 2 rows); two or one K

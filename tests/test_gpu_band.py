@@ -25,3 +25,16 @@ pytestmark = pytest.mark.gpu
 ], ids=_id)
 def test_band_wgrad(case):
     check_conv3d(case)
+
+
+# maps of 96 to 127 voxels and rows of 5 to 7: from 2^18 volumes times channel
+# pairs on this kernel, below that the gather kernel
+@pytest.mark.parametrize("case", [
+    (16, 128, 128, 4, 4, 6, 3, 1, 1, False, "bf16"),
+    (64, 64, 64, 4, 4, 7, 3, 1, 1, False, "bf16"),
+    (16, 128, 128, 5, 4, 5, 3, 1, 1, True, "bf16"),
+    (15, 128, 128, 5, 5, 5, 3, 1, 1, False, "bf16"),
+    (2, 64, 64, 5, 5, 5, 3, 1, 1, False, "bf16"),
+], ids=_id)
+def test_band_small(case):
+    check_conv3d(case)
