@@ -638,17 +638,17 @@ __global__ __launch_bounds__(kEwThreads) void up_fwd_any(const T* __restrict__ x
             const float c1 = c10 * (1.f - lh) + c11 * lh;
             return c0 * (1.f - l) + c1 * l;
         };
+        // (the first unit may start one element early, at the last column of row
+        // -1; outputs past either end are formed from an end's and not stored)
         int e = (int)threadIdx.x * 2 - (int)(o0 & 1);
-        int oh = byWo(max(e, 0)), ow = e - oh * Wo;
+        int oh = e < 0 ? -1 : byWo(e), ow = e - oh * Wo;
         for (; e < HWo; e += step) {
-            // (the first unit may start one element early: ow = -1; outputs past
-            // either end are formed from an end's and not stored)
             int h1 = oh, w1 = ow + 1;
             if (w1 >= Wo) {
                 w1 = 0;
                 ++h1;
             }
-            const float v0 = at(oh, max(ow, 0));
+            const float v0 = at(max(oh, 0), ow);
             const float v1 = at(min(h1, Ho - 1), w1);
             if (e >= 0 && e + 2 <= HWo) {
                 if constexpr (sizeof(T) == 2)

@@ -40,7 +40,10 @@ def test_maxpool_any(case):
 # this error except next to zero.
 EXACT = [((23, 28, 23), (46, 56, 46)), ((6, 5, 9), (8, 8, 12)), ((4, 6, 10), (2, 3, 5)),
          ((3, 3, 3), (3, 3, 3)), ((5, 5, 15), (8, 8, 16)), ((1, 1, 1), (3, 2, 3)),
-         ((2, 60, 50), (4, 120, 100))]
+         ((2, 60, 50), (4, 120, 100)),
+         # rows of one voxel, planes of an odd number of them, more than the 512
+         # outputs that a block forms at a time
+         ((1, 601, 1), (2, 601, 1)), ((3, 2402, 1), (3, 1201, 1))]
 ANY = [((23, 28, 23), (46, 55, 46)), ((7, 5, 9), (13, 10, 17)), ((4, 6, 5), (2, 3, 4)),
        ((2, 3, 5), (6, 8, 14)), ((9, 4, 2), (10, 5, 2))]
 
