@@ -584,19 +584,19 @@ __global__ __launch_bounds__(kEwThreads) void up_fwd_any(const T* __restrict__ x
     extern __shared__ __align__(16) float rows[];  // [maxpl][Hi][Wo], then the tables
     const int L = xcd_remap(blockIdx.x, gridDim.x);
     const int nc = L / nblk, od0 = (L - nc * nblk) * kUpPl, np = min(kUpPl, Do - od0);
-    int* h01 = reinterpret_cast<int*>(rows + maxpl * Hi * Wo);  // h0 | h1 << 16
-    int* w01 = h01 + Ho;
+    uint32_t* h01 = reinterpret_cast<uint32_t*>(rows + maxpl * Hi * Wo);  // h0 | h1 << 16
+    uint32_t* w01 = h01 + Ho;
     float* lhs = reinterpret_cast<float*>(w01 + Wo);
     float* lws = lhs + Ho;
     for (int i = threadIdx.x; i < Ho; i += kEwThreads) {
         int a, b;
         lin_src(i, Hi, sh, a, b, lhs[i]);
-        h01[i] = a | b << 16;
+        h01[i] = (uint32_t)a | (uint32_t)b << 16;
     }
     for (int i = threadIdx.x; i < Wo; i += kEwThreads) {
         int a, b;
         lin_src(i, Wi, sw, a, b, lws[i]);
-        w01[i] = a | b << 16;
+        w01[i] = (uint32_t)a | (uint32_t)b << 16;
     }
     int dlo, dhi;  // coarse planes of the first and last output plane
     {
@@ -612,7 +612,7 @@ __global__ __launch_bounds__(kEwThreads) void up_fwd_any(const T* __restrict__ x
     const int nrow = (dhi - dlo + 1) * Hi;  // consecutive rows of the volume
     for (int e = threadIdx.x; e < nrow * Wo; e += kEwThreads) {
         const int r = byWo(e), ow = e - r * Wo;
-        const int w = w01[ow];
+        const uint32_t w = w01[ow];
         const float lw = lws[ow];
         const T* row = xv + (int64_t)r * Wi;
         rows[e] = Elt<T>::ld(row + (w & 0xffff)) * (1.f - lw) + Elt<T>::ld(row + (w >> 16)) * lw;
@@ -630,9 +630,9 @@ __global__ __launch_bounds__(kEwThreads) void up_fwd_any(const T* __restrict__ x
         const float* p0 = rows + (da - dlo) * PR;
         const float* p1 = rows + (db - dlo) * PR;
         auto at = [&](int oh, int ow) {
-            const int h = h01[oh];
+            const uint32_t h = h01[oh];
             const float lh = lhs[oh];
-            const int r0 = (h & 0xffff) * Wo + ow, r1 = (h >> 16) * Wo + ow;
+            const int r0 = (int)(h & 0xffff) * Wo + ow, r1 = (int)(h >> 16) * Wo + ow;
             const float c00 = p0[r0], c01 = p0[r1], c10 = p1[r0], c11 = p1[r1];
             const float c0 = c00 * (1.f - lh) + c01 * lh;
             const float c1 = c10 * (1.f - lh) + c11 * lh;
@@ -2016,8 +2016,9 @@ rat3d_status up_fwd(int N, int C, int Di, int Hi, int Wi, int Do, int Ho, int Wo
     const size_t lds_u = up_any_lds(Di, Hi, Do, Ho, Wo);
     // (small planes leave most of its threads idle: 3x4 -> 6x7, 1024 planes, 7.2 us
     // against 6.8 for one thread per output)
-    if (Ho * Wo >= 256 && (int64_t)Ho * Wo * kUpPl < 65536 && (int64_t)up_any_planes(Di, Do) * Hi * Wo < 65536 &&
-        lds_u <= kPlaneLds) {
+    // (coarse columns are held in 16 bits; the LDS bounds the rows)
+    if (Ho * Wo >= 256 && (int64_t)Ho * Wo * kUpPl < 65536 && Wi <= 65536 &&
+        (int64_t)up_any_planes(Di, Do) * Hi * Wo < 65536 && lds_u <= kPlaneLds) {
         const int nblk = (int)ceil_div(Do, kUpPl);
         const unsigned grid = (unsigned)((int64_t)N * C * nblk);
         const int maxpl = up_any_planes(Di, Do);

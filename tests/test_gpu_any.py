@@ -43,7 +43,9 @@ EXACT = [((23, 28, 23), (46, 56, 46)), ((6, 5, 9), (8, 8, 12)), ((4, 6, 10), (2,
          ((2, 60, 50), (4, 120, 100)),
          # rows of one voxel, planes of an odd number of them, more than the 512
          # outputs that a block forms at a time
-         ((1, 601, 1), (2, 601, 1)), ((3, 2402, 1), (3, 1201, 1))]
+         ((1, 601, 1), (2, 601, 1)), ((3, 2402, 1), (3, 1201, 1)),
+         # columns beyond 15 and 16 bits
+         ((1, 1, 40000), (1, 1, 256)), ((2, 3, 65536), (4, 4, 64)), ((1, 1, 80000), (1, 1, 256))]
 ANY = [((23, 28, 23), (46, 55, 46)), ((7, 5, 9), (13, 10, 17)), ((4, 6, 5), (2, 3, 4)),
        ((2, 3, 5), (6, 8, 14)), ((9, 4, 2), (10, 5, 2))]
 
