@@ -74,7 +74,7 @@ struct FdBox {
     int kmax;                // entries of the tap tables
     int wrows;               // staged weight rows
     int xtot;                // LDS floats of the staged channels
-    int zero;                // whether a channel of zeros follows them
+    int zero;                // LDS floats of the channel of zeros behind them (0: none)
 };
 
 // One axis of a residue class: target position of index m is s m + r, its
@@ -131,7 +131,7 @@ __global__ __launch_bounds__(256, 2) void conv_box_fwd(FdBox a) {
     // take one pass), LDS byte offsets of the chunk's entries and of the taps,
     // source offsets of the staged positions
     float* xs = lds;
-    float* wsm = xs + a.xtot + (a.zero ? a.chs : 0);
+    float* wsm = xs + a.xtot + a.zero;
     const int ws_row = KC + 8;
     int* koff = (int*)(wsm + CT * 16 * ws_row);
     int* toff = koff + KC;
@@ -154,8 +154,7 @@ __global__ __launch_bounds__(256, 2) void conv_box_fwd(FdBox a) {
                         (unsigned)h < (unsigned)a.Sh && (unsigned)w < (unsigned)a.Sw;
         poff[i] = ok ? 4u * (uint32_t)((int)(n * a.Cs * Vs) + (d * a.Sh + h) * a.Sw + w) : kNoOff;
     }
-    if (a.zero)
-        for (int i = tid; i < a.chs; i += 256) xs[a.xtot + i] = 0.f;
+    for (int i = tid; i < a.zero; i += 256) xs[a.xtot + i] = 0.f;
 
     // this lane's voxels: LDS address, and target offset (-1: not a voxel)
     const char* vb[VT];
@@ -390,7 +389,7 @@ __global__ __launch_bounds__(256, 2) void conv_box_dgrad(FdBox a) {
     // LDS: staged channels (one more, all zero, for K entries past the end),
     // weights [k][WS], then the tables
     float* xs = lds;
-    float* wsm = xs + a.xtot + (a.zero ? a.chs : 0);
+    float* wsm = xs + a.xtot + a.zero;
     int* koff = (int*)(wsm + (a.wrows >> 2) * WS4);    // LDS byte offset of (channel, tap)
     uint32_t* wtap = (uint32_t*)(koff + a.kmax);      // weight byte offset of (channel, tap)
     uint32_t* poff = wtap + a.kmax;                   // source byte offset of a staged position
@@ -422,8 +421,7 @@ __global__ __launch_bounds__(256, 2) void conv_box_dgrad(FdBox a) {
                         (unsigned)h < (unsigned)a.Sh && (unsigned)w < (unsigned)a.Sw;
         poff[i] = ok ? 4u * (uint32_t)((int)(n * a.Cs * Vs) + (d * a.Sh + h) * a.Sw + w) : kNoOff;
     }
-    if (a.zero)
-        for (int i = tid; i < a.chs; i += 256) xs[a.xtot + i] = 0.f;
+    for (int i = tid; i < a.zero; i += 256) xs[a.xtot + i] = 0.f;
 
     // this lane's voxels: LDS offset, and target offset (-1: not a voxel)
     const int wv = wave % WV, wk = wave / WV;
@@ -956,7 +954,8 @@ FdPlan make_fwd_plan(const ConvGeom& g) {
         }
         f.chs = f.box.TN * ((f.box.TD - 1) * g.s + g.k) * ((f.box.TH - 1) * g.s + g.k) *
                 ((f.box.TW - 1) * g.s + g.k);
-        f.zero = K % 16 ? 1 : 0;
+        // (whole 16-byte units: the weights and offsets behind it are read in those)
+        f.zero = K % 16 ? (f.chs + 3) & ~3 : 0;
         f.blocks_x = (int)f.box.count();
         f.blocks_y = (int)ceil_div(g.Co, f.ct * 16);
         f.classes = 1;
@@ -967,7 +966,7 @@ FdPlan make_fwd_plan(const ConvGeom& g) {
             const int span = (NT - 1 + kc - 1) / NT + 1, ck = span < g.Ci ? span : g.Ci;
             const size_t xtot = ((size_t)ck * f.chs + 255) & ~(size_t)255;
             const size_t lds =
-                sizeof(float) * (xtot + f.chs * (1 + f.zero) + (size_t)f.ct * 16 * (kc + 8) + kc +
+                sizeof(float) * (xtot + f.chs + f.zero + (size_t)f.ct * 16 * (kc + 8) + kc +
                                  ((NT + 3) & ~3));
             if (xtot > kFwdXr * 256 || lds > 52 * 1024 || ck * Vs * 4 >= kLim) continue;
             const double groups = (K + 15) / 16, chunks = (double)ceil_div(K, kc);
@@ -1022,12 +1021,12 @@ FdPlan make_dgrad_plan(const ConvGeom& g) {
         f.chs = f.box.TN * (f.box.TD - 1 + n) * (f.box.TH - 1 + n) * (f.box.TW - 1 + n);
         auto bytes = [&](int ck) {
             f.xtot = (ck * f.chs + 255) & ~255;
-            f.zero = f.classes > 1 || ck * NT % 4 ? 1 : 0;  // (a class may have fewer taps)
+            f.zero = f.classes > 1 || ck * NT % 4 ? f.chs : 0;  // (a class may have fewer taps)
             f.wrows = (ck * NT + 15) & ~15;
             f.kmax = ((ck * NT + 3) & ~3) + 12 * f.wk;      // two steps are read ahead
             // (the weights' read-ahead runs over the tables behind them)
             const size_t tables = 2 * (size_t)f.kmax + f.chs, ahead = 2 * (size_t)f.wk * WS4;
-            return sizeof(float) * ((size_t)f.xtot + f.chs * f.zero + (size_t)(f.wrows / 4) * WS4 +
+            return sizeof(float) * ((size_t)f.xtot + f.zero + (size_t)(f.wrows / 4) * WS4 +
                                     (tables > ahead ? tables : ahead));
         };
         // source channels per chunk: what the staging registers and 52 KB of
@@ -1315,3 +1314,28 @@ rat3d_status conv_wgrad_box(const ConvGeom& g, const void* x, const void* dy, fl
 }
 
 }  // namespace rat3d
+
+// What a float32 convolution pass is planned as, for the tests that keep every
+// built shape of workgroup covered and the launches within their limits.
+// Returns 0 where the pass does not take these kernels, else 1 and out = {CT,
+// VT, WK or (weight gradient) CT, JT, PR; grid x, y, z; LDS bytes; LDS offset of
+// the operand rows that are read 16 bytes at a time (forward), else 0}.
+extern "C" int rat3d_box_plan(const rat3d_conv3d_desc* desc, int pass, int64_t out[8]) {
+    using namespace rat3d;
+    ConvGeom g;
+    if (!desc || !out || check_conv_desc(desc, &g) != RAT3D_OK) return 0;
+    if (pass == 2) {
+        if (!box_wgrad_ok(g, desc->dtype)) return 0;
+        const WgPlan& f = wg_plan(g);
+        const int64_t o[8] = {f.ct, f.jt, f.pr, ceil_div(g.Co, f.ct * 16), ceil_div(g.Ci, f.CI),
+                              f.splits, (int64_t)f.lds, 0};
+        for (int i = 0; i < 8; ++i) out[i] = o[i];
+        return 1;
+    }
+    if (!box_fd_ok(g, desc->dtype, pass == 1)) return 0;
+    const FdPlan& f = fd_plan(g, pass == 1);
+    const int64_t o[8] = {f.ct, f.vt, f.wk, f.blocks_x, f.blocks_y, f.classes, (int64_t)f.lds,
+                          pass == 0 ? 4 * ((int64_t)f.xtot + f.zero) : 0};
+    for (int i = 0; i < 8; ++i) out[i] = o[i];
+    return 1;
+}
