@@ -38,6 +38,9 @@ namespace {
 constexpr int kBoxMaxK = 7;
 constexpr size_t kBoxLds = 64 * 1024;
 constexpr int64_t kLim = (int64_t)1 << 31;  // 32-bit element offsets
+// Launch limits: work-items of the first dimension in 32 bits, workgroups of
+// the others in 16
+constexpr int64_t kGridX = (((int64_t)1 << 32) - 1) / 256, kGridYZ = 65535;
 
 __device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
@@ -959,6 +962,7 @@ FdPlan make_fwd_plan(const ConvGeom& g) {
         f.blocks_x = (int)f.box.count();
         f.blocks_y = (int)ceil_div(g.Co, f.ct * 16);
         f.classes = 1;
+        if (f.box.count() > kGridX || f.blocks_y > kGridYZ) continue;
         // K entries per chunk: what the staging registers and 52 KB of LDS
         // hold, by the same measure
         const int k16 = (K + 15) & ~15;
@@ -1050,6 +1054,7 @@ FdPlan make_dgrad_plan(const ConvGeom& g) {
         if (f.lds < red) f.lds = red;
         f.blocks_x = (int)f.box.count();
         f.blocks_y = (int)ceil_div(g.Ci, f.ct * 16);
+        if (f.box.count() > kGridX || f.blocks_y > kGridYZ || f.classes > kGridYZ) continue;
         const double wgs = (double)ceil_div((int64_t)f.blocks_x * f.blocks_y * f.classes, cus);
         const double mf = 32.0 * f.ct * f.vt, lone = 1.33 * mf > 130 ? 1.33 * mf : 130;
         const double chunks = (double)ceil_div(g.Co, f.CK), ksteps = (double)g.Co * NT / 4 / f.wk;
@@ -1074,11 +1079,13 @@ struct WgPlan {
 };
 
 // Splits whose partial sums the general path's workspace would hold, or 24
-// MiB of it where that is more (the allocation-free entry point has 32).
+// MiB of it where that is more (the allocation-free entry point has 32), and
+// no more than one launch takes.
 int64_t wg_splits_max(const ConvGeom& g) {
     const int64_t one = (int64_t)g.Co * g.Ci * g.k * g.k * g.k * sizeof(float);
     const int64_t a = (int64_t)wgrad_gather_ws(g) / one, b = ((int64_t)24 << 20) / one;
-    return a > b ? a : b;
+    const int64_t m = a > b ? a : b;
+    return m < kGridYZ ? m : kGridYZ;
 }
 
 WgPlan make_wg_plan(const ConvGeom& g) {
@@ -1104,6 +1111,7 @@ WgPlan make_wg_plan(const ConvGeom& g) {
     // 32-bit byte offsets: channels of a box through the scalar offset
     if ((int64_t)f.ct * 16 * Vo * 4 >= kLim) return f;
     const int64_t boxes = f.box.count(), most = wg_splits_max(g);
+    if (boxes >= kLim / 2) return f;  // (box indices are ints)
     double best = 0;
     for (int jt : {1, 2, 4, 7}) {
         // the most input channels jt column tiles per wave hold
@@ -1119,6 +1127,7 @@ WgPlan make_wg_plan(const ConvGeom& g) {
         // chain of one workgroup's boxes, two workgroups side by side) plus
         // writing and adding the partial sums at about 4.5 TB/s
         const int64_t groups = ceil_div(g.Co, f.ct * 16) * ceil_div(g.Ci, ci);
+        if (ceil_div(g.Co, f.ct * 16) > kGridX || ceil_div(g.Ci, ci) > kGridYZ) continue;
         const double mf = f.ct * jt * 32.0 * (kWgVox / 4);
         const double lone = 1.3 * mf > 160 * kWgVox / 4 ? 1.3 * mf : 160 * kWgVox / 4;
         const double words = f.ct * 16 * kWgVox / 256.0 + f.pr * ci;

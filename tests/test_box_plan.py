@@ -30,3 +30,19 @@ def box_plan(case, pass_):
 def test_forward_rows_are_16_byte_aligned(case):
     plan = box_plan(case, 0)
     assert plan is not None and plan[7] > 0 and plan[7] % 16 == 0, plan
+
+
+@pytest.mark.parametrize("case,pass_", [
+    ((33372, 3, 16, 64, 25, 146, 2, 2, 1, False), 0),   # 19.5 M ragged boxes
+    ((36, 4, 2, 1755, 14, 4979, 5, 1, 1, False), 1),    # 17.5 M
+    ((3606, 8, 1, 123, 78, 116, 2, 1, 1, False), 2),    # few weights: 83436 splits
+    ((93669, 1, 1, 41, 154, 41, 2, 1, 1, False), 2),    # 635321
+    ((2, 4, 8, 9, 11, 10, 3, 1, 1, False), 0), ((2, 4, 8, 9, 11, 10, 3, 1, 1, False), 1),
+    ((2, 4, 8, 9, 11, 10, 3, 1, 1, False), 2),
+], ids=str)
+def test_launches_within_limits(case, pass_):
+    """Less than 2^32 work-items along x and 2^16 workgroups along y and z, or
+    the general kernels."""
+    plan = box_plan(case, pass_)
+    assert plan is None or (plan[3] * 256 < 2 ** 32 and max(plan[4:6]) <= 65535), plan
+    assert plan is not None or case[0] > 2
