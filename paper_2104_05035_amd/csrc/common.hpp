@@ -117,7 +117,9 @@ __device__ __forceinline__ int xcd_remap(int bid, int nb) {
     return (bid & 7) * q + (bid >> 3);
 }
 
-// i / d for 0 <= i, d < 2^16 by one multiplication; the reciprocal is wave-uniform.
+// i / d for 0 <= i and i d < 2^32 by one multiplication; the reciprocal, 2^32 / d
+// rounded up, is wave-uniform (by less than 1, so i times it errs by less than
+// i / 2^32 < 1 / d, too little to reach the next whole number).
 struct Div {
     uint32_t d, m;
     __device__ __forceinline__ explicit Div(int x) : d((uint32_t)x), m(x > 1 ? 0xffffffffu / x + 1 : 0) {}

@@ -1200,7 +1200,10 @@ bool box_fd_ok(const ConvGeom& g, rat3d_dtype dt, bool dgrad) {
     if (!dgrad && g.Ci == 1 && g.k > 3) return false;
     const int64_t Vs = dgrad ? (int64_t)g.Do * g.Ho * g.Wo : (int64_t)g.D * g.H * g.W;
     const int64_t Vd = dgrad ? (int64_t)g.D * g.H * g.W : (int64_t)g.Do * g.Ho * g.Wo;
-    if (Vs >= kLim || Vd >= kLim || (int64_t)g.Co * g.Ci * g.k * g.k * g.k * 4 >= kLim) return false;
+    const int64_t NT = (int64_t)g.k * g.k * g.k;
+    if (Vs >= kLim || Vd >= kLim || (int64_t)g.Co * g.Ci * NT * 4 >= kLim) return false;
+    // (a K entry's channel: Div's range, with a chunk's entries past the end)
+    if (!dgrad && (g.Ci * NT + 16 * kFwdWr) * NT >= (int64_t)1 << 32) return false;
     return fd_plan(g, dgrad).ok;
 }
 

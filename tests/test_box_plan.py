@@ -46,3 +46,18 @@ def test_launches_within_limits(case, pass_):
     plan = box_plan(case, pass_)
     assert plan is None or (plan[3] * 256 < 2 ** 32 and max(plan[4:6]) <= 65535), plan
     assert plan is not None or case[0] > 2
+
+
+@pytest.mark.parametrize("c_in,k,taken", [
+    (97720, 7, False), (36506, 7, True), (36507, 7, False), (600, 7, True), (60000, 3, True)])
+def test_forward_division_range(c_in, k, taken):
+    """A K entry's channel comes from i * ceil(2^32 / k^3) >> 32, exact while
+    i k^3 < 2^32; entries up to 96 past the last are divided too."""
+    nt = k ** 3
+    plan = box_plan((1, c_in, 1, 7, 7, 7, k, 1, k // 2, False), 0)
+    assert (plan is not None) == taken
+    if taken:
+        m = -(-2 ** 32 // nt)
+        last = c_in * nt + 96
+        for i in [*range(max(0, last - 2 * nt), last), *range(0, last, max(1, last // 4096))]:
+            assert i * m >> 32 == i // nt, i
