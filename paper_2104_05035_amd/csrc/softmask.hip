@@ -13,6 +13,7 @@ namespace rat3d {
 
 constexpr int kEwThreads = 256;
 constexpr size_t kPlaneLds = 65536;  // dynamic LDS limit of the staged kernels
+constexpr int64_t kMaxBlocks = (((int64_t)1 << 32) - 1) / kEwThreads;  // of one launch
 
 // ---------------------------------------------------------------- max pool
 template <typename T>
@@ -1959,7 +1960,7 @@ rat3d_status pool_bwd(int N, int C, int D, int H, int W, int k, int s, int p, ra
         return RAT3D_OK;
     }
     const int kpa = k == 3 && s == 2 && p == 1 ? pool_any_kp(H, W, Do, Ho, Wo) : 0;
-    if (kpa > 0) {
+    if (kpa > 0 && (int64_t)N * C * ceil_div(D, 2 * kpa) <= kMaxBlocks) {
         const int nblk = (int)ceil_div(D, 2 * kpa);
         const unsigned grid = (unsigned)((int64_t)N * C * nblk);
         const size_t lds = (size_t)2 * kpa * H * W * sizeof(float);
@@ -2084,7 +2085,8 @@ rat3d_status up_bwd(int N, int C, int Di, int Hi, int Wi, int Do, int Ho, int Wo
     // voxel at 2048 x 3x4x3 -> 6x7x6, and gain less than a third below this size)
     int pl = (int64_t)Do * Ho * Wo >= 8192 ? kUpTapPl : 0;
     while (pl > 0 && up_bwd_any_lds(pl, Hi, Wi, Ho, Wo) > kPlaneLds) --pl;
-    if (pl > 0 && (int64_t)pl * Ho * Wi < 65536 && (int64_t)pl * Hi * Wi < 65536) {
+    if (pl > 0 && (int64_t)pl * Ho * Wi < 65536 && (int64_t)pl * Hi * Wi < 65536 &&
+        (int64_t)N * C * ceil_div(Di, pl) <= kMaxBlocks) {
         const int nblk = (int)ceil_div(Di, pl);
         const unsigned grid = (unsigned)((int64_t)N * C * nblk);
         const size_t lds = up_bwd_any_lds(pl, Hi, Wi, Ho, Wo);

@@ -5,6 +5,7 @@ one, resampling by less than 1, to the same size and by almost 3, planes too
 large for the staged kernels."""
 import pytest
 
+from tests import gpu_util as U
 from tests.test_gpu_ops import test_bn as check_bn
 from tests.test_gpu_ops import test_maxpool as check_maxpool
 from tests.test_gpu_ops import test_trilinear as check_trilinear
@@ -55,3 +56,46 @@ ANY = [((23, 28, 23), (46, 55, 46)), ((7, 5, 9), (13, 10, 17)), ((4, 6, 5), (2, 
                          ids=lambda v: v if isinstance(v, str) else "%s_to_%s" % v)
 def test_trilinear_any(sizes, dt):
     check_trilinear(sizes, dt)
+
+
+# More blocks than one launch takes (2^24 of 256 threads): the general kernels.
+# The planes are copies of a few, so the result is that of the few; dy holds small
+# integers, whose pooled sums are exact in any order.
+def _planes(t, c):
+    return t.repeat(1, -(-c // t.shape[1]), 1, 1, 1)[:, :c].contiguous()
+
+
+def test_maxpool_many_planes():
+    from paper_2104_05035_amd import rat3d as R
+    torch = U.torch_mod()
+    few, many = 4096, 2 ** 24 + 8
+    torch.manual_seed(1)
+    x = torch.randn(1, few, 1, 4, 8, device="cuda")
+    y, am = torch.empty(1, few, 1, 2, 4, device="cuda"), \
+        torch.empty(1, few, 1, 2, 4, dtype=torch.uint8, device="cuda")
+    R.rat3d_softmask_down_fwd(R.PoolDesc(1, few, 1, 4, 8, 3, 2, 1, R.F32), x, y, am)
+    dy = torch.randint(-8, 9, y.shape, device="cuda").float()
+    dx = {}
+    for c in (few, many):
+        dx[c] = torch.full((1, c, 1, 4, 8), 7.0, device="cuda")
+        R.rat3d_softmask_down_bwd(R.PoolDesc(1, c, 1, 4, 8, 3, 2, 1, R.F32), _planes(dy, c),
+                                  _planes(am, c), dx[c], 0)
+    U.sync()
+    assert torch.equal(dx[many], _planes(dx[few], many))
+
+
+def test_trilinear_many_planes():
+    """8193 fine planes of one voxel from 2731: sums of up to three products,
+    to within their roundings."""
+    from paper_2104_05035_amd import rat3d as R
+    torch = U.torch_mod()
+    few, many = 64, 12288
+    torch.manual_seed(2)
+    dy = torch.randn(1, few, 8193, 1, 1, device="cuda")
+    dx = {}
+    for c in (few, many):
+        dx[c] = torch.full((1, c, 2731, 1, 1), 7.0, device="cuda")
+        R.rat3d_softmask_up_bwd(R.UpDesc(1, c, 2731, 1, 1, 8193, 1, 1, R.F32), _planes(dy, c), dx[c], 0)
+    U.sync()
+    ref = _planes(dx[few], many)
+    assert float((dx[many] - ref).abs().max()) <= 8 * 2.0 ** -24 * 6 * float(dy.abs().max())
