@@ -1078,12 +1078,15 @@ struct WgPlan {
     size_t lds;
 };
 
-// Splits whose partial sums the general path's workspace would hold, or 24
-// MiB of it where that is more (the allocation-free entry point has 32), and
-// no more than one launch takes.
+// Splits whose partial sums the general path's workspace would hold, or 24 MiB
+// of it where that is more, or what the bias gradient's sums leave of the
+// bytes of the weight gradient without a workspace, which so refuses no more
+// than with the general kernel; and no more than one launch takes.
 int64_t wg_splits_max(const ConvGeom& g) {
     const int64_t one = (int64_t)g.Co * g.Ci * g.k * g.k * g.k * sizeof(float);
-    const int64_t a = (int64_t)wgrad_gather_ws(g) / one, b = ((int64_t)24 << 20) / one;
+    const int64_t left = (int64_t)kNoallocBytes - 256 - (int64_t)bias_grad_ws(g);
+    const int64_t cap = (int64_t)24 << 20;
+    const int64_t a = (int64_t)wgrad_gather_ws(g) / one, b = (left < cap ? left : cap) / one;
     const int64_t m = a > b ? a : b;
     return m < kGridYZ ? m : kGridYZ;
 }

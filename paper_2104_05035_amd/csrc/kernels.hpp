@@ -29,6 +29,9 @@ rat3d_status check_conv_desc(const rat3d_conv3d_desc* d, ConvGeom* g);
 rat3d_status check_act(const void* p, const char* name);
 
 // ---- convolution: dispatch (conv.cpp) ----------------------------------
+// Bytes that the weight gradient without a workspace argument has per device
+// (noalloc.hip).
+constexpr size_t kNoallocBytes = (size_t)32 << 20;
 // Workspace bytes of a pass (0 fwd, 1 dgrad, 2 wgrad).
 size_t conv_ws_bytes(const ConvGeom& g, rat3d_dtype dt, int pass);
 // Public-layout entry points: w is [Co][Ci][k^3] in dtype dt.

@@ -17,10 +17,9 @@
 
 namespace {
 
-constexpr size_t kScratchBytes = (size_t)32 << 20;  // 32 MiB per device
 constexpr int kMaxDevices = 64;
 
-static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+static __device__ __align__(256) unsigned char scratch[rat3d::kNoallocBytes];
 
 std::mutex g_scratch_mu;
 void* g_scratch_ptr[kMaxDevices] = {};
@@ -53,7 +52,7 @@ using namespace rat3d;
 
 extern "C" {
 
-size_t rat3d_conv3d_wgrad_noalloc_max_bytes(void) { return kScratchBytes; }
+size_t rat3d_conv3d_wgrad_noalloc_max_bytes(void) { return kNoallocBytes; }
 
 rat3d_status rat3d_conv3d_wgrad_noalloc(const rat3d_conv3d_desc* desc, const void* x,
                                         const void* dy, float* dw, float* dbias, int accumulate,
@@ -67,15 +66,15 @@ rat3d_status rat3d_conv3d_wgrad_noalloc(const rat3d_conv3d_desc* desc, const voi
         return RAT3D_EINVAL;
     }
     const size_t need = conv_ws_bytes(g, desc->dtype, 2);
-    if (need > kScratchBytes) {
+    if (need > kNoallocBytes) {
         set_error("conv3d_wgrad_noalloc: this shape needs %zu bytes of scratch, more than the "
                   "%zu built in; use rat3d_conv3d_wgrad with a workspace",
-                  need, kScratchBytes);
+                  need, kNoallocBytes);
         return RAT3D_EWORKSPACE;
     }
     void* ptr = nullptr;
     if ((s = scratch_address(&ptr)) != RAT3D_OK) return s;
-    return conv_wgrad(g, desc->dtype, x, dy, dw, dbias, accumulate ? 1 : 0, ptr, kScratchBytes,
+    return conv_wgrad(g, desc->dtype, x, dy, dw, dbias, accumulate ? 1 : 0, ptr, kNoallocBytes,
                       (hipStream_t)stream);
 }
 

@@ -61,3 +61,15 @@ def test_forward_division_range(c_in, k, taken):
         last = c_in * nt + 96
         for i in [*range(max(0, last - 2 * nt), last), *range(0, last, max(1, last // 4096))]:
             assert i * m >> 32 == i // nt, i
+
+
+@pytest.mark.parametrize("case", [
+    (39589, 194, 76, 12, 7, 9, 2, 3, 1, True), (33049, 96, 69, 5, 9, 9, 3, 1, 2, True),
+    (28968, 48, 75, 4, 4, 7, 3, 1, 0, True)], ids=str)
+def test_noalloc_keeps_what_it_took(case):
+    """Batches whose bias-gradient sums leave less than 24 MiB for the partial
+    sums: the weight gradient without a workspace argument still takes them."""
+    desc = R.conv_desc(*case[:9], case[9], R.F32)
+    assert box_plan(case, 2) is not None
+    need = R.rat3d_conv3d_workspace_size(desc, 2)
+    assert need <= R.lib().rat3d_conv3d_wgrad_noalloc_max_bytes(), need
