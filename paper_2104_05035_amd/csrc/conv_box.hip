@@ -880,23 +880,23 @@ struct Box {
 // box only where it holds the whole map.
 bool pick_box(int N, int D, int H, int W, int vox, int S, int n, int maxp, Box* out) {
     int64_t best = -1;
-    auto next = [](int L, int parts) { return (int)ceil_div(L, parts); };
-    for (int jw = 1, lw = 0; jw <= W; ++jw) {
-        const int TW = next(W, jw);
-        if (TW == lw || TW > vox) continue;
-        lw = TW;
-        for (int jh = 1, lh = 0; jh <= H; ++jh) {
-            const int TH = next(H, jh);
-            if (TH == lh || TH * TW > vox) continue;
-            lh = TH;
+    auto next = [](int L, int parts) { return (int)(((unsigned)L + parts - 1) / (unsigned)parts); };
+    // lengths of the balanced cuts of an axis, from the longest that fits down
+    // (no more steps than the box has voxels, however long the axis is)
+    for (int tw = W < vox ? W : vox; tw >= 1; --tw) {
+        const int TW = next(W, next(W, tw));
+        if (TW != tw) continue;
+        for (int th = H < vox / TW ? H : vox / TW; th >= 1; --th) {
+            const int TH = next(H, next(H, th));
+            if (TH != th) continue;
             const int room = vox / (TW * TH);
-            const int TD = next(D, (int)ceil_div(D, room));
+            const int TD = next(D, next(D, room));
             const int PW = (TW - 1) * S + n, PH = (TH - 1) * S + n, PD = (TD - 1) * S + n;
             int TN = 1;
             if (TD == D && TH == H && TW == W) {
                 TN = vox / (D * H * W);
                 if (TN > N) TN = N;
-                TN = next(N, (int)ceil_div(N, TN));
+                TN = next(N, next(N, TN));
                 while (TN > 1 && (int64_t)TN * PD * PH * PW > maxp) --TN;
             }
             const int64_t P = (int64_t)TN * PD * PH * PW;

@@ -1,6 +1,7 @@
 """Plans of the float32 voxel-box convolutions (host side, no GPU needed): the
 layout and the launches they ask for stay within what the kernels assume."""
 import ctypes
+import time
 
 import pytest
 
@@ -73,3 +74,14 @@ def test_noalloc_keeps_what_it_took(case):
     assert box_plan(case, 2) is not None
     need = R.rat3d_conv3d_workspace_size(desc, 2)
     assert need <= R.lib().rat3d_conv3d_wgrad_noalloc_max_bytes(), need
+
+
+def test_plans_of_long_axes_take_little_time():
+    """A plan looks at no more boxes than one has voxels, so an axis of a
+    million voxels costs a first call (three plans) well under the 0.2 to 0.8 s of
+    a search over every number of cuts."""
+    t0 = time.perf_counter()
+    for i, size in enumerate([(1, 2000000, 14), (4, 700001, 10), (3, 1000003, 9)]):
+        for pass_ in range(3):
+            assert box_plan((1, 2, 3, *size, 3, 1, 1, False), pass_) is not None, (i, pass_)
+    assert time.perf_counter() - t0 < 0.1
