@@ -934,6 +934,56 @@ double box_cycles(double wgs, double side, double mfma, double chain, double chu
     return mul > ceil(wgs / side) * one ? mul : ceil(wgs / side) * one;
 }
 
+// Microseconds of a pass on the gather kernels (conv_gather.hip), fitted to
+// their times of 10320 random layers (k 1, 2, 3, 5, 7, strides 1 to 3, 1 to 256
+// channels, 1 to 125 voxels per axis; 7 to 19 % off at one standard deviation).
+double gather_us(const ConvGeom& g, int pass) {
+    const int cus = device_cus();
+    const double NT = g.k * g.k * g.k, Vo = (double)g.N * g.Do * g.Ho * g.Wo;
+    auto up = [](double a, double b) { return ceil(a / b); };
+    if (pass == 0) {
+        const double steps = up(g.Ci * NT, 16), w = up(up(Vo, 64) * up(g.Co, 64), cus);
+        return 3.9 + 1.0 * steps + w * (0.33 + 0.418 * steps) + 0.45 * 4e-6 * g.Co * Vo;
+    }
+    if (pass == 1 && g.s == 1) {
+        const double steps = up(g.Co * NT, 16);
+        const double w = up(up((double)g.N * g.D * g.H * g.W, 64) * up(g.Ci, 64), cus);
+        const double mb = 4e-6 * g.N * g.Ci * (double)g.D * g.H * g.W;
+        return 4.3 + 1.45 * steps + w * (0.35 + 0.741 * steps) + 0.33 * mb;
+    }
+    if (pass == 1) {  // residue classes, of n taps per axis or one fewer, and strided stores
+        const double n = up(g.k, g.s), classes = (double)g.s * g.s * g.s;
+        const double rows = (double)g.N * up(g.D, g.s) * up(g.H, g.s) * up(g.W, g.s);
+        const double tiles = up(rows, 64) * up(g.Ci, 64) * classes;
+        const double mb = 4e-6 * g.N * g.Ci * (double)g.D * g.H * g.W;
+        return 5.4 + 1.51 * up(g.Co * n * n * n, 16) +
+               tiles / cus * (0.84 + 0.45 * g.Co * NT / 16 / classes) + 0.34 * g.s * mb;
+    }
+    const double one = (double)g.Co * g.Ci * NT, tiles = up(g.Co, 64) * up(g.Ci * NT, 64);
+    const double want = (double)(wgrad_gather_ws(g) / sizeof(float)) / one;
+    const double steps = up(up(Vo, want), 16), splits = up(Vo, 16 * steps);
+    return 3.8 + 1.34 * steps + up(tiles * splits, cus) * 0.415 * steps + 3.5e-6 * one * (splits + 1);
+}
+// The same of a pass planned here: `fixed`, a lone workgroup's tables, first
+// loads and stores; then the planned cycles (us, at 2.4 GHz) beyond it, of
+// which `share` remains (residue classes have fewer taps than the largest), or
+// the megabytes of the 64-byte lines that the staged and the stored (weight
+// gradient: dy) rows touch: a box of short rows costs the MFMAs nothing and
+// moves up to sixteen times its voxels.  A plan is taken where it is expected to
+// be faster, by the margin of the pass.  Of those layers a plan taken whenever
+// there was one was more than 5 % slower than the gather kernel for 4 % of the
+// forward, 5 % of the input and 26 % of the weight gradients (8 x 32 -> 32, 1^3,
+// 60x50x77 forward 271 and 1100 us; 4 x 96 -> 128, 7^3 stride 3, 27x21x35
+// weight gradient 623 and 1069).  With this rule, 16, 39 and 20 of 3464 further
+// layers (1.46, 1.57 and 1.44 times at most), and the time of all of them is
+// within 0.2 % of what the faster kernel of each would take.
+constexpr double kTake[3] = {1.0, 0.95, 0.9};
+double box_us(double fixed, double cycles_us, double share, double staged_mb, double stored_mb) {
+    const double a = cycles_us > fixed ? share * (cycles_us - fixed) : 0;
+    const double b = 0.14 * staged_mb + 0.15 * stored_mb;
+    return fixed + sqrt(a * a + b * b);
+}
+
 // Shapes of workgroup that conv_box_fwd is built for: (CT, VT).
 constexpr int kFwdShapes[][2] = {{4, 2}, {2, 2}, {2, 1}, {1, 4}, {1, 1}};
 
@@ -992,6 +1042,16 @@ FdPlan make_fwd_plan(const ConvGeom& g) {
                 best_cost = cost;
             }
         }
+    }
+    if (best.ok) {
+        const Box& b = best.box;
+        const double rows = (double)b.count() * b.TN * ((b.TD - 1) * g.s + g.k) *
+                            ((b.TH - 1) * g.s + g.k) * best.blocks_y * g.Ci;
+        const double staged = 4e-6 * rows * ((b.TW - 1) * g.s + g.k + 15);
+        const double stored = 4e-6 * g.N * g.Co * (double)g.Do * g.Ho * g.Wo * (b.TW + 15) / b.TW;
+        // (1^3: tables of one tap and boxes without halo: half of the cycles planned)
+        best.ok = box_us(5.5, best_cost / 2400, g.k == 1 ? 0.5 : 1.0, staged, stored) <
+                  kTake[0] * gather_us(g, 0);
     }
     return best;
 }
@@ -1066,6 +1126,18 @@ FdPlan make_dgrad_plan(const ConvGeom& g) {
             best.ok = true;
             best_cost = cost;
         }
+    }
+    if (best.ok) {
+        const Box& b = best.box;
+        const double rows = (double)b.count() * b.TN * (b.TD - 1 + n) * (b.TH - 1 + n) *
+                            best.blocks_y * best.classes * g.Co;
+        // products of an average class against the largest
+        const double f = (double)g.k * g.k * g.k / ((double)best.classes * NT);
+        const double staged = 4e-6 * rows * f * (b.TW - 1 + n + 15);
+        // (a class stores every s-th word of a row)
+        const double stored = 4e-6 * g.N * g.Ci * (double)g.D * g.H * g.W * (b.TW * g.s + 15) / b.TW;
+        best.ok = box_us(7.0, best_cost / 2400, 1.1 * (0.4 + 0.6 * f), staged, stored) <
+                  kTake[1] * gather_us(g, 1);
     }
     return best;
 }
@@ -1152,6 +1224,16 @@ WgPlan make_wg_plan(const ConvGeom& g) {
                 f.ok = true;
             }
         }
+    }
+    if (f.ok) {
+        const Box& b = f.box;
+        const double rows = (double)boxes * b.TN * PD * PH * ceil_div(g.Co, f.ct * 16) * g.Ci;
+        const double dyrows =
+            (double)boxes * b.TN * b.TD * b.TH * ceil_div(g.Ci, f.CI) * g.Co;
+        const double us =
+            box_us(7.0, best, 1.0, 4e-6 * rows * (PW + 15), 4e-6 * dyrows * (b.TW + 15)) +
+            3.6e-6 * f.splits * g.Co * g.Ci * KT;
+        f.ok = us < kTake[2] * gather_us(g, 2);
     }
     return f;
 }
