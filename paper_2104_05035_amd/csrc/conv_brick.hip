@@ -585,10 +585,22 @@ __global__ __launch_bounds__(512, 1) void conv_brick_fd(FdArgs a) {
     // and add them before the single rounding; the producers' stores stay
     // plain bf16 stores.
     const bool split_out = a.nsplit > 1;
+    // A workgroup of one tile has nothing to drain it behind: staged, every such
+    // launch of 32 source channels took 19.9 us, by elements from the lanes 14.1 to
+    // 18 (5 x 32 -> 32 at 3x4x4 forward 19.9 and 14.9, at 10x5x6 19.9 and 17.3; of
+    // four columns a row, with element staging too).  Tiles of 32 channels
+    // from 32 have one step each, and rows whose last tile holds four columns
+    // move as many units as whole ones for it: 8 x 32 -> 32 at 65x42x68 input
+    // gradient 169 staged, 121 direct, forward 169 and 147; 10 x 32 -> 32 at
+    // 41x49x20 77 and 67; with other ends or 64 channels staged is as fast or
+    // faster (7 x 32 -> 32 at 47x48x28 51.7 and 56.5; 10 x 32 -> 64 at 40x47x20
+    // 77 and 106).
+    const bool lone = a.ntiles <= (int)gridDim.x;
+    const bool tail4 = NT == 2 && a.cps == 1 && (a.W & 15) == 4;
     // (drained by the owners of the group items, so not with element staging)
-    const bool elem = !W8 && elem_rows(a.W);
+    const bool elem = !W8 && (elem_rows(a.W) || (a.W == 4 && lone && a.cps == 1));
     const bool staged_epi = !split_out && (!ACC || KS == 3) &&
-                            (W8 || (KS == 3 && (a.W & 1) == 0 && !elem));
+                            (W8 || (KS == 3 && (a.W & 1) == 0 && !elem && !lone && !tail4));
     using OldV = uint2[ACC ? NR : 1][ACC ? CT : 1];
     auto load_old = [&](int k, OldV& o) {
         const Tile T = tile_of(k);
@@ -774,7 +786,8 @@ __global__ __launch_bounds__(512, 1) void conv_brick_fd(FdArgs a) {
             __builtin_amdgcn_sched_barrier(0);
         }
     };
-    // direct epilogue (odd widths; 1^3: accumulating or not a multiple of 8):
+    // direct epilogue (odd widths, lone tiles and last tiles of four columns; 1^3:
+    // accumulating or not a multiple of 8):
     // lane holds 4 consecutive w of one output channel per tile row
     auto direct_outputs = [&](int k) {
         const Tile T = tile_of(k);

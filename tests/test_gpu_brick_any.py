@@ -24,3 +24,13 @@ def test_brick_any_width(w, c):
 ], ids=_id)
 def test_brick_any_case(case):
     check_conv3d(case)
+
+
+# Even widths with several tiles per workgroup (more than 256 tiles): results
+# leave through LDS, in 16-byte units and 4-byte ones at a row's end; with 32
+# source channels and rows whose last tile holds four columns (W = 4, 20), and
+# with one tile per workgroup (above), straight from the lanes.
+@pytest.mark.parametrize("w,c", [(4, 32), (6, 32), (10, 32), (12, 32), (14, 32), (18, 32), (20, 32),
+                                 (22, 32), (6, 64), (14, 64), (20, 64)])
+def test_brick_even_many_tiles(w, c):
+    check_conv3d((140, c, c, 5, 3, w, 3, 1, 1, c == 32, "bf16"))
