@@ -1135,7 +1135,14 @@ rat3d_status conv_wgrad_gather(const ConvGeom& g, rat3d_dtype dt, const void* x,
     {
     ProfScope ps("conv_gather_wgrad", st, conv_flops(g),
                  conv_bytes(g, dt == RAT3D_BF16 ? 2 : 4));
-    if (dt == RAT3D_BF16 && g.k <= 7 && pipe_narrow(g))
+    // Few live rows of a tile's 64 + 64 over many voxels: the plain kernel loads
+    // nothing for the others, the pipelined one issues every load (us, plain and
+    // pipelined: 1^3, 5 x 8 -> 8 at 83x82x111 218 and 279, 8 x 12 -> 12 at 87x76x76
+    // 242 and 302, 5 x 20 -> 20 at 66x59x62 98 and 109; 3^3, 16 x 1 -> 1 at 88x88x104
+    // 859 and 967; 4 x 4 -> 8 at 42x40x49 37 and 40; with more rows or fewer voxels the
+    // pipelined one is as fast or faster: 3^3, 16 x 2 -> 2 at 70x105x102 947 and 852)
+    const bool sparse = g.Co + Ncols <= 48 && Ktot >= 320000;
+    if (dt == RAT3D_BF16 && g.k <= 7 && pipe_narrow(g) && !sparse)
         conv_gather_wgrad_pipe<<<grid, 256, 0, st>>>(g, (const bf16*)x, (const bf16*)dy, part,
                                                      (int)kchunk);
     else if (dt == RAT3D_BF16)

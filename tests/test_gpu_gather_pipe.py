@@ -25,3 +25,15 @@ pytestmark = pytest.mark.gpu
 ], ids=_id)
 def test_gather_pipe(case):
     check_conv3d(case)
+
+
+# few live rows of a tile over 320000 voxels and more, where the weight gradient
+# is the plain kernel's, and just below either line
+@pytest.mark.parametrize("case", [
+    (5, 3, 4, 40, 40, 41, 1, 1, 0, True, "bf16"),
+    (6, 1, 2, 38, 38, 38, 3, 1, 1, False, "bf16"),
+    (5, 3, 4, 39, 40, 41, 1, 1, 0, False, "bf16"),
+    (6, 1, 24, 38, 38, 38, 3, 1, 1, False, "bf16"),
+], ids=_id)
+def test_gather_few_rows(case):
+    check_conv3d(case)
