@@ -563,13 +563,23 @@ __global__ __launch_bounds__(kEwThreads) void pool332_bwd_any(const T* __restric
 // threads and a tile of at most 40 KB.
 // (planes of a few voxels: 2048 x 3x4x3 took 9.6 us against 7.4 for one thread
 // per voxel, 2048 x 6x7x6 9.7 against 11.0)
-static int pool_any_kp(int H, int W, int Do, int Ho, int Wo) {
+// A block is a chain of some microseconds, so few of them (up to 64 or so, 128
+// with tiles of 4 KB and less) lose against one thread per voxel: 4 x 2 at
+// 29x16x32 4.7 us per voxel and 10.4 so, 1 x 32 at 17x24x14 5.5 and 7.0, 16 x 2 at
+// 19x28x20 6.8 and 10.3.  Both times as fitted to 2040 random maps (10 and 15 %
+// off at one standard deviation); taken whenever possible it was more than 5 %
+// slower on 645 of them, by this rule on 3.
+static int pool_any_kp(int64_t NC, int D, int H, int W, int Do, int Ho, int Wo) {
     const int64_t hw = (int64_t)H * W, per = (int64_t)Ho * Wo;
     if (hw < 32 || hw >= 65536 || per >= 32768) return 0;  // (Div's range)
     int64_t kp = 40960 / (2 * hw * 4);
     if (kp > Do) kp = Do;
     while (kp >= 1 && (kp + 1) * per > (int64_t)kAnyWin * kEwThreads) --kp;
-    return (int)kp;
+    if (kp < 1) return 0;
+    const double blocks = (double)NC * ceil_div(D, 2 * kp), tile = 2.0 * kp * hw / 256;
+    if (blocks > kMaxBlocks) return 0;
+    const double here = 4.8 + 0.096 * tile + (0.049 * tile + 0.46) * blocks / 256;
+    return here < 0.95 * (4.2 + 8.3e-6 * NC * D * hw) ? (int)kp : 0;
 }
 
 // Trilinear upsampling: a block owns kUpPl output planes.  Phase A blends the
@@ -678,6 +688,23 @@ static int up_any_planes(int Di, int Do) {
 static size_t up_any_lds(int Di, int Hi, int Do, int Ho, int Wo) {
     return ((size_t)up_any_planes(Di, Do) * Hi * Wo + 2 * (size_t)(Ho + Wo)) * sizeof(float);
 }
+// Few blocks leave the chip idle while each blends its rows in turn, and an axis
+// that shrinks leaves rows unread that it blends all the same: 1 x 4 at 22x42x32
+// -> 33x85x64 4.9 us with one thread per output and 23.6 so, 16 x 1 at 25x19x33 ->
+// 26x29x66 5.4 and 12.4, 4 x 4 at 6x48x16 -> 4x14x32 2.5 and 10.4.  Both times
+// as fitted to 3524 random maps (11 and 16 % off at one standard deviation);
+// taken whenever possible it was more than 5 % slower on 1446 of them, by this
+// rule on 35.
+static bool up_any_pays(int64_t NC, int es, int Di, int Hi, int Wi, int Do, int Ho, int Wo) {
+    const double blocks = (double)NC * ceil_div(Do, kUpPl);
+    const double rounds_a = (double)ceil_div((int64_t)up_any_planes(Di, Do) * Hi * Wo, kEwThreads);
+    const double rounds_b = (double)kUpPl * ceil_div((int64_t)Ho * Wo, 2 * kEwThreads);
+    const double here = 3.0 + (0.128 * rounds_a + 0.195 * rounds_b) * (1 + 0.427 * blocks / 256);
+    const bool tables = Ho <= kAxisMax && Wo <= kAxisMax && NC * Do < 65536;
+    const double each = 2.45 + (tables ? 3.66e-6 : 5.3e-6) * NC * Do * Ho * Wo +
+                        0.066e-6 * es * NC * Di * Hi * Wi;
+    return here < each;
+}
 
 // Its transpose: a block owns pl coarse planes.  Phase A sums the fine planes
 // they receive from, weighted along the depth, into LDS; phase B sums along
@@ -773,6 +800,26 @@ __global__ __launch_bounds__(kEwThreads) void up_bwd_any(const T* __restrict__ d
 }
 static size_t up_bwd_any_lds(int pl, int Hi, int Wi, int Ho, int Wo) {
     return (size_t)pl * Ho * (Wo + Wi) * sizeof(float) + (size_t)(pl + Hi + Wi) * sizeof(AxisTaps);
+}
+// Its three phases in turn against one thread per coarse voxel, whose time grows
+// with the taps of a voxel: where few blocks or axes that hardly grow leave it
+// little to save it loses (1 x 1 at 42x41x58 -> 42x81x117 11.5 us per voxel, 25.7
+// so; 2 x 2 at 55x37x42 -> 109x74x42 14.5 and 26.2; 1 x 20 at 28x19x33 -> 28x18x32
+// 8.8 and 11.0).  Both times as fitted to 2993 random maps (11 and 18 % off at
+// one standard deviation); taken whenever possible it was more than 5 % slower
+// on 262 of them, by this rule on 35.
+static bool up_bwd_any_pays(int64_t NC, int pl, int Di, int Hi, int Wi, int Do, int Ho, int Wo) {
+    auto taps = [](int in, int out) { return 2.0 * out > in ? 2.0 * out / in : 1.0; };
+    const double td = taps(Di, Do), th = taps(Hi, Ho), tw = taps(Wi, Wo);
+    const double blocks = (double)NC * ceil_div(Di, pl), vox = 1e-6 * NC * Di * Hi * Wi;
+    const double planes = (double)(pl + 1) * Do / Di + 1 < Do ? (double)(pl + 1) * Do / Di + 1 : Do;
+    const double rounds_a = (double)ceil_div((int64_t)Ho * Wo, 4 * kEwThreads) * ceil(planes / 2);
+    const double rounds_b = (double)ceil_div((int64_t)pl * Ho * Wi, kEwThreads) * tw;
+    const double rounds_c = (double)ceil_div((int64_t)pl * Hi * Wi, kEwThreads) * th;
+    const double here = 8.2 + (0.294 * rounds_a + 0.057 * rounds_b + 0.136 * rounds_c) *
+                                  (1 + 0.5 * blocks / 256);
+    const double fill = 3.8 * vox > 1 ? 3.8 * vox : 1;  // rounds of the chip, at least one
+    return here < 0.95 * (5.3 + 0.21 * td * th * tw * fill + 6.07 * vox + 0.14 * td * th);
 }
 
 // ---------------------------------------------------------------- exact x2, bf16
@@ -1940,10 +1987,14 @@ rat3d_status pool_bwd(int N, int C, int D, int H, int W, int k, int s, int p, ra
     const unsigned blocks = (unsigned)ceil_div(total, kEwThreads);
     const double es = dt == RAT3D_BF16 ? 2.0 : 4.0;
     const double small = (double)N * C * Do * Ho * Wo;
-    ProfScope ps("pool_bwd", st, 0.0, es * (small + total * (1 + accumulate)) + small);
     const size_t lds_b = (size_t)(kPlanes + 1) * Ho * Wo * 3;
-    const int kp = k == 3 && s == 2 && p == 1 && dt == RAT3D_BF16 ? pool_sc_kp(D, H, W, Do, Ho, Wo)
-                                                                  : 0;
+    const bool k332 = k == 3 && s == 2 && p == 1;
+    const int kp = k332 && dt == RAT3D_BF16 ? pool_sc_kp(D, H, W, Do, Ho, Wo) : 0;
+    const bool plane = k332 && dt == RAT3D_BF16 && W % 8 == 0 && lds_b <= kPlaneLds;
+    const int kpa =
+        k332 && kp == 0 && !plane ? pool_any_kp((int64_t)N * C, D, H, W, Do, Ho, Wo) : 0;
+    ProfScope ps(kpa > 0 ? "pool_bwd_any" : "pool_bwd", st, 0.0,
+                 es * (small + total * (1 + accumulate)) + small);
     if (kp > 0) {
         const int nblk = (int)ceil_div(D, 2 * kp);
         pool332_bwd_sc<<<(unsigned)((int64_t)N * C * nblk), kEwThreads,
@@ -1952,15 +2003,14 @@ rat3d_status pool_bwd(int N, int C, int D, int H, int W, int k, int s, int p, ra
         RAT3D_LAUNCH_CHECK();
         return RAT3D_OK;
     }
-    if (k == 3 && s == 2 && p == 1 && dt == RAT3D_BF16 && W % 8 == 0 && lds_b <= kPlaneLds) {
+    if (plane) {
         const int nblk = (int)ceil_div(D, 2 * kPlanes);
         pool332_bwd_pl<<<(unsigned)((int64_t)N * C * nblk), kEwThreads, lds_b, st>>>(
             (const bf16*)dy, argmax, D, H, W, Do, Ho, Wo, nblk, (bf16*)dx, accumulate);
         RAT3D_LAUNCH_CHECK();
         return RAT3D_OK;
     }
-    const int kpa = k == 3 && s == 2 && p == 1 ? pool_any_kp(H, W, Do, Ho, Wo) : 0;
-    if (kpa > 0 && (int64_t)N * C * ceil_div(D, 2 * kpa) <= kMaxBlocks) {
+    if (kpa > 0) {
         const int nblk = (int)ceil_div(D, 2 * kpa);
         const unsigned grid = (unsigned)((int64_t)N * C * nblk);
         const size_t lds = (size_t)2 * kpa * H * W * sizeof(float);
@@ -2003,23 +2053,27 @@ rat3d_status up_fwd(int N, int C, int Di, int Hi, int Wi, int Do, int Ho, int Wo
     const int64_t total = (int64_t)N * C * Do * Ho * Wo;
     const unsigned blocks = (unsigned)ceil_div(total, kEwThreads);
     const float sd = up_scale(Di, Do), sh = up_scale(Hi, Ho), sw = up_scale(Wi, Wo);
-    ProfScope ps("up_fwd", st, 0.0,
-                 (dt == RAT3D_BF16 ? 2.0 : 4.0) * ((double)N * C * Di * Hi * Wi + total));
     const bool x2 = Do == 2 * Di && Ho == 2 * Hi && Wo == 2 * Wi;
     const size_t lds_f = (size_t)2 * kPlanes * ((Hi * Wi + 7) & ~7) * sizeof(float);
-    if (x2 && dt == RAT3D_BF16 && Wi % 4 == 0 && lds_f <= kPlaneLds) {
+    const bool plane = x2 && dt == RAT3D_BF16 && Wi % 4 == 0 && lds_f <= kPlaneLds;
+    const size_t lds_u = up_any_lds(Di, Hi, Do, Ho, Wo);
+    // (small planes leave most of its threads idle: 3x4 -> 6x7, 1024 planes, 7.2 us
+    // against 6.8 for one thread per output)
+    // (coarse columns are held in 16 bits; the LDS bounds the rows)
+    const bool any =
+        !plane && Ho * Wo >= 256 && (int64_t)Ho * Wo * kUpPl < 65536 && Wi <= 65536 &&
+        (int64_t)up_any_planes(Di, Do) * Hi * Wo < 65536 && lds_u <= kPlaneLds &&
+        up_any_pays((int64_t)N * C, dt == RAT3D_BF16 ? 2 : 4, Di, Hi, Wi, Do, Ho, Wo);
+    ProfScope ps(any ? "up_fwd_any" : "up_fwd", st, 0.0,
+                 (dt == RAT3D_BF16 ? 2.0 : 4.0) * ((double)N * C * Di * Hi * Wi + total));
+    if (plane) {
         const int nblk = (int)ceil_div(Di, kPlanes);
         up2_fwd_pl<false><<<(unsigned)((int64_t)N * C * nblk), kEwThreads, lds_f, st>>>(
             (const bf16*)x, Di, Hi, Wi, nblk, (bf16*)y, UpStats{});
         RAT3D_LAUNCH_CHECK();
         return RAT3D_OK;
     }
-    const size_t lds_u = up_any_lds(Di, Hi, Do, Ho, Wo);
-    // (small planes leave most of its threads idle: 3x4 -> 6x7, 1024 planes, 7.2 us
-    // against 6.8 for one thread per output)
-    // (coarse columns are held in 16 bits; the LDS bounds the rows)
-    if (Ho * Wo >= 256 && (int64_t)Ho * Wo * kUpPl < 65536 && Wi <= 65536 &&
-        (int64_t)up_any_planes(Di, Do) * Hi * Wo < 65536 && lds_u <= kPlaneLds) {
+    if (any) {
         const int nblk = (int)ceil_div(Do, kUpPl);
         const unsigned grid = (unsigned)((int64_t)N * C * nblk);
         const int maxpl = up_any_planes(Di, Do);
@@ -2060,13 +2114,22 @@ rat3d_status up_bwd(int N, int C, int Di, int Hi, int Wi, int Do, int Ho, int Wo
     const int64_t total = (int64_t)N * C * Di * Hi * Wi;
     const unsigned blocks = (unsigned)ceil_div(total, kEwThreads);
     const float sd = up_scale(Di, Do), sh = up_scale(Hi, Ho), sw = up_scale(Wi, Wo);
-    ProfScope ps("up_bwd", st, 0.0,
-                 (dt == RAT3D_BF16 ? 2.0 : 4.0) *
-                     ((double)N * C * Do * Ho * Wo + total * (1 + accumulate)));
     const bool x2 = Do == 2 * Di && Ho == 2 * Hi && Wo == 2 * Wi;
     const size_t lds_b = (size_t)kPlanes * Ho * Wo * sizeof(float);
-    if (x2 && dt == RAT3D_BF16 && up2_roll_ok(Hi, Wi) &&
-        (size_t)2 * Ho * Wo * sizeof(float) <= kPlaneLds) {
+    const bool roll = x2 && dt == RAT3D_BF16 && up2_roll_ok(Hi, Wi) &&
+                      (size_t)2 * Ho * Wo * sizeof(float) <= kPlaneLds;
+    const bool plane = x2 && dt == RAT3D_BF16 && Wi % 4 == 0 && lds_b <= kPlaneLds;
+    // (small volumes: its three phases take 28 us against 21 for one thread per
+    // voxel at 2048 x 3x4x3 -> 6x7x6, and gain less than a third below this size)
+    int pl = !roll && !plane && (int64_t)Do * Ho * Wo >= 8192 ? kUpTapPl : 0;
+    while (pl > 0 && up_bwd_any_lds(pl, Hi, Wi, Ho, Wo) > kPlaneLds) --pl;
+    const bool any = pl > 0 && (int64_t)pl * Ho * Wi < 65536 && (int64_t)pl * Hi * Wi < 65536 &&
+                     (int64_t)N * C * ceil_div(Di, pl) <= kMaxBlocks &&
+                     up_bwd_any_pays((int64_t)N * C, pl, Di, Hi, Wi, Do, Ho, Wo);
+    ProfScope ps(any ? "up_bwd_any" : "up_bwd", st, 0.0,
+                 (dt == RAT3D_BF16 ? 2.0 : 4.0) *
+                     ((double)N * C * Do * Ho * Wo + total * (1 + accumulate)));
+    if (roll) {
         const int nchunk = (int)ceil_div(Di, kUpChunk);
         up2_bwd_roll<false><<<(unsigned)((int64_t)N * C * nchunk), kEwThreads,
                               (size_t)2 * Ho * Wo * sizeof(float), st>>>(
@@ -2074,19 +2137,14 @@ rat3d_status up_bwd(int N, int C, int Di, int Hi, int Wi, int Do, int Ho, int Wo
         RAT3D_LAUNCH_CHECK();
         return RAT3D_OK;
     }
-    if (x2 && dt == RAT3D_BF16 && Wi % 4 == 0 && lds_b <= kPlaneLds) {
+    if (plane) {
         const int nblk = (int)ceil_div(Di, kPlanes);
         up2_bwd_pl<false><<<(unsigned)((int64_t)N * C * nblk), kEwThreads, lds_b, st>>>(
             (const bf16*)dy, Di, Hi, Wi, nblk, (bf16*)dx, accumulate, UpBn{});
         RAT3D_LAUNCH_CHECK();
         return RAT3D_OK;
     }
-    // (small volumes: its three phases take 28 us against 21 for one thread per
-    // voxel at 2048 x 3x4x3 -> 6x7x6, and gain less than a third below this size)
-    int pl = (int64_t)Do * Ho * Wo >= 8192 ? kUpTapPl : 0;
-    while (pl > 0 && up_bwd_any_lds(pl, Hi, Wi, Ho, Wo) > kPlaneLds) --pl;
-    if (pl > 0 && (int64_t)pl * Ho * Wi < 65536 && (int64_t)pl * Hi * Wi < 65536 &&
-        (int64_t)N * C * ceil_div(Di, pl) <= kMaxBlocks) {
+    if (any) {
         const int nblk = (int)ceil_div(Di, pl);
         const unsigned grid = (unsigned)((int64_t)N * C * nblk);
         const size_t lds = up_bwd_any_lds(pl, Hi, Wi, Ho, Wo);
