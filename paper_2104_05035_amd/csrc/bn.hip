@@ -385,14 +385,21 @@ __global__ __launch_bounds__(kBnThreads) void bn_bwd_apply(
 // Whether planes of V elements that are no whole vectors (VEC == 1) take the
 // ODD apply: below 1024 one block of 256 elements per plane or two are quicker
 // than vectors with their partial ends (the full network's 36- and
-// 252-element planes: its step 6.47 ms, 6.55 with vectors).
-template <int VEC> static bool bn_odd_vec(int64_t V) { return VEC == 1 && V >= 1024; }
+// 252-element planes: its step 6.47 ms, 6.55 with vectors).  Tensors of fewer
+// elements than these leave most CUs without a block of vectors (bf16 forward,
+// by elements and by vectors: 8 x 4 at 13x12x9 5.4 and 6.2 us, 16 x 1 at 23x17x29
+// 6.6 and 7.8; up to 400000 elements 3 to 20 % slower, from 800000 on 15 to 55 %
+// faster; float32, four elements to a vector, breaks even at half of it).
+template <typename T, int VEC> static bool bn_odd_vec(const BnGeom& g) {
+    return VEC == 1 && g.V >= 1024 &&
+           (int64_t)g.N * g.C * g.V >= (sizeof(T) == 2 ? 400000 : 200000);
+}
 
 // Blocks per plane of an apply pass, u vectors per thread; an odd plane may
 // lie in one more vector than it fills.
-template <typename T, int VEC> static unsigned bn_chunks(int64_t V, int u) {
+template <typename T, int VEC> static unsigned bn_chunks(const BnGeom& g, int u) {
     constexpr int AV = vec16<T>();
-    const int64_t vecs = bn_odd_vec<VEC>(V) ? (V + 2 * AV - 2) / AV : V / VEC;
+    const int64_t vecs = bn_odd_vec<T, VEC>(g) ? (g.V + 2 * AV - 2) / AV : g.V / VEC;
     return (unsigned)ceil_div(vecs, (int64_t)kBnThreads * u);
 }
 
@@ -416,8 +423,8 @@ static rat3d_status bn_fwd_t(const BnGeom& g, int relu, float eps, float momentu
     const BnFwdStats fs{part,     sl.per_channel, gamma,   beta,   eps,      momentum,
                         save_mean, save_invstd,   run_mean, run_var, save_coef};
     const int fu = r ? fwd_apply_u<1>() : fwd_apply_u<0>();
-    const bool odd = bn_odd_vec<VEC>(g.V);
-    const unsigned cpp = bn_chunks<T, VEC>(g.V, fu);  // chunks per plane
+    const bool odd = bn_odd_vec<T, VEC>(g);
+    const unsigned cpp = bn_chunks<T, VEC>(g, fu);  // chunks per plane
     const unsigned grid = cpp * (unsigned)(g.N * g.C);
     ProfScope ps("bn_fwd_apply", st, 0.0, tb * (r ? 3 : 2) + (ybits ? tb / 16 : 0.0));
 #define RAT3D_BN_FWD(RL, RS)                                                                 \
@@ -464,8 +471,8 @@ static rat3d_status bn_bwd_t(const BnGeom& g, int relu, const T* dy, const T* x,
     RAT3D_LAUNCH_CHECK();
     }
     const BnBwdStats bs{part, sl.per_channel, gamma, save_invstd, dgamma, dbeta, accumulate};
-    const bool odd = bn_odd_vec<VEC>(g.V);
-    const unsigned cpp = bn_chunks<T, VEC>(g.V, kBwdApplyU);  // chunks per plane
+    const bool odd = bn_odd_vec<T, VEC>(g);
+    const unsigned cpp = bn_chunks<T, VEC>(g, kBwdApplyU);  // chunks per plane
     const unsigned grid = cpp * (unsigned)(g.N * g.C);
     ProfScope ps("bn_bwd_apply", st, 0.0,
                  tb * (3 + (dres ? (dres_acc ? 2 : 1) : 0)) + mb);

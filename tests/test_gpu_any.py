@@ -19,6 +19,9 @@ pytestmark = pytest.mark.gpu
     (2, 3, 7, 9, 11, "bf16"), (3, 5, 1, 1, 1, "bf16"), (2, 3, 1, 1, 9, "bf16"),
     (2, 2, 13, 15, 23, "bf16"), (1, 3, 19, 21, 25, "bf16"), (2, 3, 7, 9, 11, "f32"),
     (2, 2, 13, 15, 23, "f32"), (3, 3, 1, 1, 5, "f32"), (5, 1, 1, 2, 1, "f32"),
+    # in vectors: 400000 elements (bf16) and 200000 (float32) in planes of 1024 or more
+    (7, 55, 5, 11, 19, "bf16"), (3, 31, 13, 15, 23, "bf16"), (1, 5, 43, 45, 47, "bf16"),
+    (9, 22, 5, 11, 19, "f32"), (1, 3, 41, 43, 45, "f32"),
 ], ids=lambda c: "%dx%dx%dx%dx%d_%s" % c)
 @pytest.mark.parametrize("relu,resid", [(1, False), (0, False), (1, True), (0, True)])
 def test_bn_odd(case, relu, resid):
