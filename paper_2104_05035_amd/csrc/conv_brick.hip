@@ -585,18 +585,20 @@ __global__ __launch_bounds__(512, 1) void conv_brick_fd(FdArgs a) {
     // and add them before the single rounding; the producers' stores stay
     // plain bf16 stores.
     const bool split_out = a.nsplit > 1;
-    // A workgroup of one tile has nothing to drain it behind: staged, every such
-    // launch of 32 source channels took 19.9 us, by elements from the lanes 14.1 to
-    // 18 (5 x 32 -> 32 at 3x4x4 forward 19.9 and 14.9, at 10x5x6 19.9 and 17.3; of
-    // four columns a row, with element staging too).  Tiles of 32 channels
-    // from 32 have one step each, and rows whose last tile holds four columns
-    // move as many units as whole ones for it: 8 x 32 -> 32 at 65x42x68 input
-    // gradient 169 staged, 121 direct, forward 169 and 147; 10 x 32 -> 32 at
-    // 41x49x20 77 and 67; with other ends or 64 channels staged is as fast or
-    // faster (7 x 32 -> 32 at 47x48x28 51.7 and 56.5; 10 x 32 -> 64 at 40x47x20
-    // 77 and 106).
-    const bool lone = a.ntiles <= (int)gridDim.x;
-    const bool tail4 = NT == 2 && a.cps == 1 && (a.W & 15) == 4;
+    // A few workgroups of one tile each have nothing to drain it behind: staged,
+    // every such launch of 32 source channels took 19.9 us, from the lanes the
+    // ones of rows below 8 14.1 to 18 (5 x 32 -> 32 at 3x4x4 forward 19.9 and 14.9,
+    // at 10x5x6 19.9 and 17.3; of four columns a row, with element staging too).
+    // Wider rows and more tiles gain by whole units again (16 x 96 -> 128 at 8x9x6,
+    // 128 tiles, 39.6 staged and 44.5 direct; 8 x 32 -> 256 at 11x11x14 26.6 and
+    // 31.8).  Tiles of 32 channels from 32 have one step each, and rows whose last
+    // tile holds four columns move as many units as whole ones for it: 8 x 32 -> 32
+    // at 65x42x68 input gradient 169 staged, 121 direct, forward 169 and 147; 10 x 32
+    // -> 32 at 41x49x20 77 and 67; with other ends or 64 channels staged is as fast
+    // or faster (7 x 32 -> 32 at 47x48x28 51.7 and 56.5; 10 x 32 -> 64 at 40x47x20 77
+    // and 106).
+    const bool lone = a.W < 8 && a.ntiles <= 64 && a.ntiles <= (int)gridDim.x;
+    const bool tail4 = NT == 2 && a.cps == 1 && (a.W & 15) == 4 && a.ntiles > (int)gridDim.x;
     // (drained by the owners of the group items, so not with element staging)
     const bool elem = !W8 && (elem_rows(a.W) || (a.W == 4 && lone && a.cps == 1));
     const bool staged_epi = !split_out && (!ACC || KS == 3) &&
