@@ -105,3 +105,51 @@ def test_plans_of_long_axes_take_little_time():
 ], ids=str)
 def test_the_faster_kernel_is_taken(case, pass_, gather, box):
     assert (box_plan(case, pass_) is not None) == (box < gather)
+
+
+# Layers whose plans take every built shape of workgroup: (case, pass, CT, VT, WK)
+# or, weight gradients, (case, 2, CT, JT, PR).  Channel counts that leave a
+# remainder of the tiles; run against the oracle in tests/test_gpu_box.py.
+COVER = [
+    ((3, 16, 48, 25, 27, 29, 3, 1, 1, False), 0, 4, 2, 1),
+    ((1, 4, 33, 31, 33, 30, 3, 1, 1, True), 0, 4, 2, 1),
+    ((2, 16, 48, 20, 21, 23, 3, 1, 1, False), 0, 2, 2, 1),
+    ((1, 4, 17, 31, 33, 30, 3, 1, 1, True), 0, 2, 2, 1),
+    ((3, 16, 64, 25, 27, 29, 3, 2, 1, False), 0, 2, 1, 1),
+    ((3, 4, 33, 13, 15, 17, 3, 1, 1, True), 0, 2, 1, 1),
+    ((1, 4, 8, 31, 33, 30, 3, 1, 1, False), 0, 1, 4, 1),
+    ((1, 17, 33, 9, 11, 13, 3, 1, 1, True), 0, 1, 1, 1),
+    ((3, 48, 16, 25, 27, 29, 3, 2, 1, False), 1, 4, 4, 1),
+    ((3, 33, 8, 25, 27, 29, 3, 2, 1, False), 1, 4, 4, 1),
+    ((3, 33, 33, 20, 21, 23, 3, 2, 1, False), 1, 4, 2, 1),
+    ((3, 33, 8, 20, 21, 23, 3, 2, 1, False), 1, 2, 4, 1),
+    ((2, 33, 8, 13, 15, 17, 3, 2, 1, False), 1, 2, 2, 1),
+    ((2, 4, 8, 20, 21, 23, 3, 2, 1, False), 1, 1, 4, 1),
+    ((2, 17, 8, 13, 15, 17, 3, 2, 1, False), 1, 2, 2, 4),
+    ((2, 4, 8, 13, 15, 17, 3, 2, 1, False), 1, 1, 2, 4),
+    ((1, 17, 33, 9, 11, 13, 3, 1, 1, True), 1, 1, 1, 4),
+    ((2, 33, 8, 13, 15, 17, 3, 1, 1, True), 2, 1, 4, 2),
+    ((1, 24, 8, 25, 27, 29, 3, 1, 1, False), 2, 1, 7, 2),
+    ((1, 12, 17, 25, 27, 29, 3, 1, 1, False), 2, 2, 4, 2),
+    ((1, 48, 17, 31, 33, 30, 3, 1, 1, False), 2, 2, 7, 2),
+    ((1, 17, 65, 13, 15, 17, 3, 1, 1, True), 2, 4, 2, 2),
+    ((2, 33, 65, 13, 15, 17, 3, 1, 1, False), 2, 4, 4, 2),
+    ((1, 48, 33, 31, 33, 30, 3, 1, 1, False), 2, 4, 7, 2),
+    ((1, 1, 70, 3, 14, 4, 5, 1, 2, False), 2, 4, 2, 4),
+    ((3, 1, 101, 1, 4, 6, 6, 1, 3, False), 2, 4, 4, 4),
+    ((3, 1, 40, 3, 5, 5, 7, 1, 3, False), 2, 4, 7, 16),
+    ((2, 1, 17, 15, 25, 1, 7, 2, 3, False), 2, 2, 7, 16),
+]
+
+
+@pytest.mark.parametrize("case,pass_,a,b,c", COVER, ids=str)
+def test_cover_takes_its_shape(case, pass_, a, b, c):
+    plan = box_plan(case, pass_)
+    assert plan is not None and plan[:3] == [a, b, c], plan
+
+
+def test_cover_has_every_forward_and_input_gradient_shape():
+    assert {c[2:] for c in COVER if c[1] == 0} == {(4, 2, 1), (2, 2, 1), (2, 1, 1), (1, 4, 1),
+                                                   (1, 1, 1)}
+    assert {c[2:] for c in COVER if c[1] == 1} == {(4, 4, 1), (4, 2, 1), (2, 4, 1), (2, 2, 1),
+                                                   (1, 4, 1), (2, 2, 4), (1, 2, 4), (1, 1, 4)}

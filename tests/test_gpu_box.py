@@ -1,10 +1,13 @@
-"""GPU parity of the float32 voxel-box convolutions at the sizes where their
-plans change: channel counts around the 16/32/64 tiles, boxes that divide the
-map or leave a remainder on each axis, several samples in one box, K split
-over waves, K entries past the end (odd channels times taps), taps staged in
-groups (7^3), residue classes with different tap counts and with none."""
+"""GPU parity of the float32 voxel-box convolutions: small layers (boxes that
+divide the map or leave a remainder on each axis, several samples in one box, K
+split over waves, K entries past the end, 7^3, residue classes with different
+tap counts and with none; some passes of them take the gather kernels), and
+layers that take every built shape of workgroup in the forward and input
+gradient and the larger ones of the weight gradient (asserted on the host in
+tests/test_box_plan.py, and again here)."""
 import pytest
 
+from tests.test_box_plan import COVER, box_plan
 from tests.test_gpu_ops import _id, test_conv3d as check_conv3d
 
 pytestmark = pytest.mark.gpu
@@ -35,3 +38,9 @@ CASES = [
 @pytest.mark.parametrize("case", CASES, ids=_id)
 def test_conv3d_box(case):
     check_conv3d(case)
+
+
+@pytest.mark.parametrize("case,pass_,a,b,c", COVER, ids=str)
+def test_conv3d_box_shapes(case, pass_, a, b, c):
+    assert box_plan(case, pass_)[:3] == [a, b, c]
+    check_conv3d(case + ("f32",))
