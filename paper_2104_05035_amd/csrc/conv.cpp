@@ -2,8 +2,9 @@
 // workspace.  bf16 stride-1 convolutions with kernel 3 (pad 1) or 1 (pad 0)
 // and suitable channel counts take the LDS-brick kernels (1^3 weight
 // gradients a direct GEMM); the single-channel 7^3 stride-2 stem has its own
-// kernels; float32 convolutions up to 7^3 take the voxel-box kernels; every
-// other shape is served by the generic gather implicit GEMM.
+// kernels; float32 convolutions up to 7^3 take the voxel-box kernels where those
+// are expected to be faster; every other shape is served by the generic gather
+// implicit GEMM.
 #include "kernels.hpp"
 
 namespace rat3d {

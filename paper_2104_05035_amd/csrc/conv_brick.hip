@@ -367,10 +367,11 @@ __global__ __launch_bounds__(512, 1) void conv_brick_fd(FdArgs a) {
     // offset, when the brick is written.  Columns past the width are zeroed.
     // Before, every brick voxel took eight 2-byte loads, waited for on the
     // spot, and the results left the consumer waves as 2-byte stores; even
-    // widths now also drain their results in 16-byte units.  Forward, before ->
+    // widths also drain their results in 16-byte units where that gains
+    // (staged_epi), odd widths still store by elements.  Forward, before ->
     // after: 4 x 64 -> 64 at 46x55x46 154.7 -> 104.1 us (989 TF), 8 x 64 at
-    // 22x26x22 72.2 -> 51.9, 8 x 128 at 12x14x12 44.7 -> 36.5; odd widths, whose
-    // stores are still by elements, 45x55x45 144.7 -> 140.9.  Widths of whole
+    // 22x26x22 72.2 -> 51.9, 8 x 128 at 12x14x12 44.7 -> 36.5; odd widths, 45x55x45,
+    // 144.7 -> 140.9.  Widths of whole
     // groups keep kernels of their own (W8): sharing one cost them 4 % of the
     // input gradient at 16 x 64, 48x56x48 (395 against 380 us).
     const bool oddw = (a.W & 1) != 0;

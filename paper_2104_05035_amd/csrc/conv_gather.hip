@@ -792,7 +792,8 @@ __global__ __launch_bounds__(256) void conv_gather_wgrad(ConvGeom g, const T* __
             }
 }
 
-// The same weight gradient in bf16, k <= 7, tensors below 2 GiB, pipelined: a
+// The same weight gradient in bf16, k <= 7, tensors below 2 GiB (but for a few
+// rows over many voxels, see the launcher), pipelined: a
 // K step's 32 voxels are table entries in LDS (a ring of four, filled two steps
 // ahead), {x element of tap 0, bits of the tap coordinates outside the volume,
 // dy element, 0}, and an operand is a buffer load at entry + column offset.

@@ -462,11 +462,12 @@ __global__ __launch_bounds__(kEwThreads) void up_bwd_tab_k(const T* __restrict__
     Elt<T>::st(dx + t, base + sum);
 }
 
-// ---------------------------------------------------------------- any size, staged
+// ---------------------------------------------------------------- other sizes, staged
 // Pooling gradient and trilinear resampling of maps that the bf16 plane
 // kernels below do not take (float32, widths that are not a multiple of 8,
-// resampling that is not an exact x2), each source element read once or
-// twice per block and the stencils finished from LDS.  Measured at 4 x 64 x
+// resampling that is not an exact x2) and that fit their LDS, where a launch
+// has enough blocks to gain by them (the rule beside each), each source
+// element read once or twice per block and the stencils finished from LDS.  Measured at 4 x 64 x
 // 46x55x46 <-> 23x28x23 in bf16 against one thread per voxel gathering its
 // taps from memory: pooling gradient 237 -> 33 us, upsampling 101 -> 42,
 // its transpose 222 -> 68.
