@@ -101,9 +101,8 @@ struct PrepBatch {
 constexpr int kPrepElems = 8 * 32 * 27;  // staged weights: 8 rows of 3^3 taps
 constexpr int kPrepPad = 8;              // elements between the staged runs' ends and starts
 constexpr int kPrepRuns = 32;            // runs, at most (target rows or source channels)
-// A layer of 32 channels is four workgroups, whose two passes over 864 units are
-// a chain of latencies: with 256 threads a forward call of it took 1.1 us more
-// than with one thread per unit, with 512 0.5 us, with 1024 0.7 us.
+// A job's few workgroups are a chain of latencies: 256 threads took 0.6 us longer
+// for a layer of 32 channels, 1024 0.2 us.
 constexpr int kPrepThreads = 512;
 
 __global__ __launch_bounds__(kPrepThreads) void prep_weights_batch(PrepBatch b) {
@@ -155,6 +154,31 @@ __global__ __launch_bounds__(kPrepThreads) void prep_weights_batch(PrepBatch b) 
     }
 }
 
+// One small layer: one thread per 16-byte unit with eight gathered reads, many
+// short blocks where the staged kernel has a few long ones.  Forward and input
+// gradient calls with it against those with the staged kernel, us: 32 -> 32 0.8
+// and 0.9 less, 64 -> 64 0.4 and 0.8, 128 -> 128 0.2 and 0.4; 128 -> 256 0.5 and
+// 0.2 more, 256 -> 256 2.0 and 1.3; 1^3 within 0.4 either way.
+constexpr int kPrepOne = 128 * 128;  // channel pairs of 3^3, at most
+__global__ __launch_bounds__(256) void prep_weights_one(const bf16* __restrict__ w,
+                                                        bf16* __restrict__ wt, int Co, int Ci,
+                                                        int KT, int dg) {
+    const int e = (int)blockIdx.x * 256 + threadIdx.x;
+    if (e >= Co * Ci / 8 * KT) return;
+    const int Ct = dg ? Ci : Co;
+    // e = ((cb * KT + t) * Ct + tc) * 4 + s8: unit s8 of chunk cb's 32 source channels
+    const int s8 = e & 3, r = e >> 2, r2 = r / Ct, tc = r - r2 * Ct, cb = r2 / KT, t = r2 - cb * KT;
+    const int s0 = cb * 32 + s8 * 8;
+    const bf16* p = w + (dg ? (s0 * Ci + tc) * KT + (KT - 1 - t) : (tc * Ci + s0) * KT + t);
+    const int step = dg ? Ci * KT : KT;
+    uint32_t v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = p[j * step];
+    *reinterpret_cast<uint4*>(wt + (int64_t)e * 8) =
+        make_uint4(v[0] | (v[1] << 16), v[2] | (v[3] << 16), v[4] | (v[5] << 16),
+                   v[6] | (v[7] << 16));
+}
+
 rat3d_status brick_prep_weights_batch(const PrepJob* jobs, int n, hipStream_t st) {
     for (int j = 0; j < n; ++j) {
         const int cs = jobs[j].dgrad ? jobs[j].g.Co : jobs[j].g.Ci;
@@ -163,6 +187,13 @@ rat3d_status brick_prep_weights_batch(const PrepJob* jobs, int n, hipStream_t st
                       "buffer 16-byte aligned and the filter no larger than 3^3", cs);
             return RAT3D_EINVAL;
         }
+    }
+    if (n == 1 && jobs[0].g.k == 3 && (int64_t)jobs[0].g.Co * jobs[0].g.Ci <= kPrepOne) {
+        const PrepJob& J = jobs[0];
+        prep_weights_one<<<(unsigned)ceil_div(J.g.Co * J.g.Ci / 8 * 27, 256), 256, 0, st>>>(
+            (const bf16*)J.w, (bf16*)J.wt, J.g.Co, J.g.Ci, 27, J.dgrad ? 1 : 0);
+        RAT3D_LAUNCH_CHECK();
+        return RAT3D_OK;
     }
     for (int j0 = 0; j0 < n; j0 += kPrepJobs) {
         PrepBatch b{};
