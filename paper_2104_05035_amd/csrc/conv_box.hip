@@ -675,6 +675,18 @@ __device__ __forceinline__ float buf_ldf_s(__amdgpu_buffer_rsrc_t r, uint32_t of
 // leave the registers free)
 __host__ __device__ constexpr int box_cs(int jt, int pr) { return (jt == 1 ? 64 : 32) / pr; }
 constexpr int kWgVox = 128;          // voxels per box
+// Whether a box's sum is formed apart and added to the range's: the error is then
+// that of sums of 128 products and of some boxes, not of one running sum over all
+// voxels of the range (against float64, with one running sum, apart, and with the
+// general kernel: 4 x 128 -> 32 at 38x52x40, stride 2, 1.2e-6, 2.3e-7 and 5.7e-7;
+// 2 x 64 -> 64 at 31x26x32 7.1e-7, 2.2e-7 and 4.7e-7).  The largest shapes have no
+// registers for it: their ranges are no longer than the general kernel's.  It costs
+// 0.6% of the time on average over 578 random layers, up to 26% (5 x 96 -> 48, 5^3,
+// stride 2, at 25x23x19: 179 and 225 us, the general kernel 261); one sum over
+// several boxes costs as much.
+__host__ __device__ constexpr bool box_two(int ct, int jt, int pr) {
+    return ct * jt <= (pr == 16 ? 8 : 16);
+}
 constexpr int kDyRow = kWgVox + 4;   // LDS floats per staged dy row: 16 rows x 4 voxels hit 64 banks
 }  // namespace
 
@@ -738,7 +750,8 @@ __global__ __launch_bounds__(256, 2) void conv_box_wgrad(WgBox a) {
         vw = r - vh * a.TW;
         vbase = 4 * (vn * P1 + (vdd * g.s * PH + vh * g.s) * PW + vw * g.s);
     }
-    f32x4 acc[CT][JT];
+    constexpr bool TWO = box_two(CT, JT, PR);
+    f32x4 acc[CT][JT], box[TWO ? CT : 1][TWO ? JT : 1];
 #pragma unroll
     for (int c = 0; c < CT; ++c)
 #pragma unroll
@@ -813,13 +826,22 @@ __global__ __launch_bounds__(256, 2) void conv_box_wgrad(WgBox a) {
 #pragma unroll
             for (int c = 0; c < CT; ++c) x[c] = al[c * 16 * kDyRow + st * 4];
         };
+        if constexpr (TWO) {
+#pragma unroll
+            for (int c = 0; c < CT; ++c)
+#pragma unroll
+                for (int j = 0; j < JT; ++j) box[c][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
         // a lane without a voxel takes part with zero (never 0 * x)
         auto mul = [&](int vo, const float (&x)[CT], const float (&y)[JT]) {
 #pragma unroll
             for (int j = 0; j < JT; ++j) {
                 const float yj = vo >= 0 ? y[j] : 0.f;
 #pragma unroll
-                for (int c = 0; c < CT; ++c) acc[c][j] = mfma4(x[c], yj, acc[c][j]);
+                for (int c = 0; c < CT; ++c) {
+                    f32x4& s = TWO ? box[TWO ? c : 0][TWO ? j : 0] : acc[c][j];
+                    s = mfma4(x[c], yj, s);
+                }
             }
         };
         auto spread = [&] {
@@ -845,6 +867,12 @@ __global__ __launch_bounds__(256, 2) void conv_box_wgrad(WgBox a) {
             spread();
             vo0 = vo2;
             vo1 = vo3;
+        }
+        if constexpr (TWO) {
+#pragma unroll
+            for (int c = 0; c < CT; ++c)
+#pragma unroll
+                for (int j = 0; j < JT; ++j) acc[c][j] += box[c][j];
         }
         __syncthreads();
     }
@@ -1203,12 +1231,17 @@ WgPlan make_wg_plan(const ConvGeom& g) {
         // writing and adding the partial sums at about 4.5 TB/s
         const int64_t groups = ceil_div(g.Co, f.ct * 16) * ceil_div(g.Ci, ci);
         if (ceil_div(g.Co, f.ct * 16) > kGridX || ceil_div(g.Ci, ci) > kGridYZ) continue;
+        // voxels of a range of the general kernel
+        const int64_t gather = ceil_div(g.N * Vo, (int64_t)(wgrad_gather_ws(g) / sizeof(float)) /
+                                                  ((int64_t)g.Co * g.Ci * KT));
+        const int64_t longest =
+            box_two(f.ct, jt, f.pr) ? boxes : gather / kWgVox > 1 ? gather / kWgVox : 1;
         const double mf = f.ct * jt * 32.0 * (kWgVox / 4);
         const double lone = 1.3 * mf > 160 * kWgVox / 4 ? 1.3 * mf : 160 * kWgVox / 4;
         const double words = f.ct * 16 * kWgVox / 256.0 + f.pr * ci;
         const double one = lone + 500 + 140 * words;  // cycles of a lone workgroup's box
-        for (int64_t per = ceil_div(boxes, most), tried = 0; per <= boxes && tried < 64;
-             ++per, ++tried) {
+        for (int64_t per = ceil_div(boxes, most), tried = 0;
+             per <= boxes && per <= longest && tried < 64; ++per, ++tried) {
             const int64_t splits = ceil_div(boxes, per);
             const double cu = (double)ceil_div(groups * splits, device_cus());
             const double a = cu * per * (mf * 1.1 + 70 * words);
