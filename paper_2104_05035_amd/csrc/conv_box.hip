@@ -22,9 +22,9 @@
 //
 // Bound: MFMA issue (153 TFLOP/s for a large float32 matrix product).  Measured
 // against the gather kernel, 3^3, 64 -> 64 channels, us: 2 x 24x28x24 forward
-// 232 -> 78 (92 TFLOP/s), input gradient 310 -> 83, weight gradient 168 -> 107;
-// 8 x 46x55x46 3576 -> 1858 (111 TFLOP/s), 5248 -> 1933, 5009 -> 2504; 2 x
-// 6x7x6, 256 channels 770 -> 105, 1017 -> 75, 68 -> 47.
+// 232 -> 78 (92 TFLOP/s), input gradient 310 -> 83, weight gradient 168 -> 109;
+// 8 x 46x55x46 3576 -> 1858 (111 TFLOP/s), 5248 -> 1933, 5009 -> 2620; 2 x
+// 6x7x6, 256 channels 770 -> 105, 1017 -> 75, 68 -> 48.
 #include <cmath>
 
 #include "common.hpp"
